@@ -163,12 +163,13 @@ int hwenou_stage(hwenou_handle* h, int s, const double* dt_dev, const double* al
  * alpha_2/dy) clipped likewise (2D), or dt = t_final - t when every wave
  * speed of the instance is zero (all fluxes vanish).  The paper fixes the
  * CFL number (0.6 in Section 3) but not the formula; this is the usual one.
- * Whole steps (the three stages and a finish kernel that also sets the next
- * dt) are replayed from a HIP graph, with alpha and dt on the device; the
- * graph is captured on the first call and kept while the state pointers and
- * the launch shape stay the same.  The host reads a completion flag after
- * each chunk of steps without waiting for the chunk in flight, and
- * synchronises at the end.  An instance whose state leaves the physical
+ * alpha and dt stay on the device.  In 1D a whole step is one launch on the
+ * handle's stream (unless an instance has exactly one periodic side); in 2D,
+ * and for such 1D handles, whole steps (the three stages and a finish kernel
+ * that also sets the next dt) are replayed from a HIP graph, which is captured
+ * on the first call and kept while the state pointers and the launch shape
+ * stay the same.  The host reads a completion flag after each chunk of steps
+ * without waiting for the chunk in flight, and synchronises at the end.  An instance whose state leaves the physical
  * states (rho <= 0, p <= 0 or non-finite, flagged by any of its kernels)
  * stops after the step in which that happened: its t_out and steps_out
  * include that step, its arrays hold that step's result, and the other

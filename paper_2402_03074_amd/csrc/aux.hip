@@ -5,6 +5,8 @@
 // in 2D, and the per-step bookkeeping of t, the step count and completion.
 // All per-instance state lives on the device so that whole steps can be
 // replayed from a captured graph without host synchronisation.
+#include <algorithm>
+
 #include "hwenou_internal.hpp"
 
 namespace hwenou {
@@ -30,8 +32,9 @@ __global__ __launch_bounds__(256) void max_wavespeed_kernel(const AuxArgs A) {
   mx = wave_max(mx);
   my = wave_max(my);
   if ((threadIdx.x & 63) == 0) {
-    atomic_max_nonneg(&A.alpha[2 * inst], mx);
-    atomic_max_nonneg(&A.alpha[2 * inst + 1], my);
+    double* acc = A.alpha + (long long)A.alpha_stride * inst;
+    atomic_max_nonneg(acc, mx);
+    atomic_max_nonneg(acc + 1, my);
   }
 }
 
@@ -40,8 +43,9 @@ __global__ void zero_alpha_kernel(double* alpha, int n) {
     alpha[k] = 0.0;
 }
 
-hipError_t launch_max_wavespeed(const AuxArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(zero_alpha_kernel, dim3(1), dim3(256), 0, s, a.alpha, 2 * a.n_inst);
+hipError_t launch_max_wavespeed(const AuxArgs& a, bool zero, hipStream_t s) {
+  if (zero)
+    hipLaunchKernelGGL(zero_alpha_kernel, dim3(1), dim3(256), 0, s, a.alpha, 2 * a.n_inst);
   // 64 blocks per instance, grid-stride over its cells
   const dim3 grid(64, a.n_inst);
   if (a.eq == EQ_ADVECTION)
@@ -170,6 +174,92 @@ hipError_t launch_dt(const AuxArgs& a, hipStream_t s) {
 
 hipError_t launch_finish(const AuxArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+// Start of a run of whole 1D steps: the call's parameters, zero time and step
+// count, no flags, and zero wave-speed accumulators.
+__global__ __launch_bounds__(256) void run_begin_kernel(const RunArgs A) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
+  if (t == 0) *A.run = A.R;
+  for (int k = t; k < A.n_inst; k += nt) {
+    A.st[0][k] = {0.0, 0, 0};
+    A.flag[0][k] = 0;
+    A.flag[1][k] = 0;
+  }
+  for (int k = t; k < A.n_inst * A.slots; k += nt)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      A.acc[b][kAlphaStride * k] = 0.0;
+      A.acc[b][kAlphaStride * k + 1] = 0.0;
+    }
+}
+
+// Between chunks of steps: whether any instance would take another step.
+__global__ __launch_bounds__(256) void run_poll_kernel(const RunArgs A) {
+  __shared__ int running;
+  if (threadIdx.x == 0) running = 0;
+  __syncthreads();
+  const RunParams R = *A.run;
+  int mine = 0;
+  for (int k = threadIdx.x; k < A.n_inst; k += blockDim.x) {
+    const StepState s = A.st[A.last][k];
+    if (!(s.done || A.flag[A.last][k] || s.steps >= R.max_steps ||
+          s.t >= R.t_final * (1.0 - 1e-14)))
+      mine = 1;
+  }
+  if (mine) atomicOr(&running, 1);
+  __syncthreads();
+  if (threadIdx.x == 0) *A.running_host = running;
+}
+
+// End of a run: the state of an instance that stopped after an odd number of
+// steps is in the scratch buffers and goes back to the caller's arrays; time,
+// step count and status go to the pinned host arrays.  One wave per tile.
+template <class TM>
+__global__ __launch_bounds__(256) void run_end_kernel(const RunArgs A) {
+  const int lane = threadIdx.x & 63, per = blockDim.x >> 6;
+  const TM* m_odd = static_cast<const TM*>(A.m_odd);
+  TM* m = static_cast<TM*>(A.m);
+  for (int it = blockIdx.x * per + (threadIdx.x >> 6); it < A.n_tiles; it += gridDim.x * per) {
+    const TileItem wk = A.tiles[it];
+    const StepState s = A.st[A.last][wk.inst];
+    const InstDev I = A.inst[wk.inst];
+    if (s.steps & 1) {
+      const int i = wk.start + lane;
+      if (lane < kStepWidth && i < I.nx) {
+        const long long o = I.offset + i;
+        for (int k = 0; k < A.nc; ++k) A.u[k * A.plane + o] = A.u_odd[k * A.plane + o];
+        for (int k = 0; k < A.mom_planes; ++k) m[k * A.plane + o] = m_odd[k * A.plane + o];
+      }
+    }
+    if (wk.start == 0 && lane == 0) {
+      const int f = A.flag[0][wk.inst] | A.flag[1][wk.inst];
+      A.status[wk.inst] = f;
+      A.t_host[wk.inst] = s.t;
+      A.steps_host[wk.inst] = s.steps;
+      A.status_host[wk.inst] = f;
+    }
+  }
+}
+
+hipError_t launch_run_begin(const RunArgs& a, hipStream_t s) {
+  const int blocks = std::min(256, (a.n_inst * a.slots + 255) / 256);
+  hipLaunchKernelGGL(run_begin_kernel, dim3(blocks), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_run_poll(const RunArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(run_poll_kernel, dim3(1), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_run_end(const RunArgs& a, hipStream_t s) {
+  const int blocks = std::min(2048, (a.n_tiles + 3) / 4);
+  if (a.mom_elem == 4)
+    hipLaunchKernelGGL(run_end_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(run_end_kernel<double>, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -7,6 +7,7 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/hwenou.h"
@@ -61,6 +62,16 @@ struct hwenou_handle {
   double *s1u = nullptr, *s2u = nullptr;
   void *s1m = nullptr, *s2m = nullptr;
   const double* u_base = nullptr;    // recorded by stage 0
+  // whole steps in one launch (1D; step1d.hip): usable when every instance has
+  // two periodic sides or none
+  bool whole_steps = false;
+  TileItem* d_tiles = nullptr;
+  int n_tiles = 0, step_waves = 0, step_slots = 1;
+  StepState* d_state = nullptr;      // [2][n_inst]
+  int* d_flag = nullptr;             // [2][n_inst]
+  double* d_acc = nullptr;           // [4][n_inst][kAlphaSlots][kAlphaStride]
+  double* h_t = nullptr;             // pinned results of a run, [n_inst] each
+  int *h_steps = nullptr, *h_status = nullptr;
   // work lists
   int waves_per_cu = 0, rows_per_item = 0;
   int n_cu = 256;
@@ -92,6 +103,8 @@ int dalloc_bytes(void** p, size_t bytes) {
   return HWENOU_OK;
 }
 
+constexpr int kStepThreads = 256;  // block of the whole-step 1D kernel
+
 // Steps per replay of the multi-step graph: the gap between two graph
 // launches (~5-10 us) then falls on every kMultiSteps-th step only, which
 // matters for grids whose steps take tens of microseconds.
@@ -117,6 +130,8 @@ void free_handle(hwenou_handle* h) {
   f(h->d_steps); f(h->d_done); f(h->d_status); f(h->d_all_done); f(h->d_run);
   f(h->m_base); f(h->s1u); f(h->s2u); f(h->s1m); f(h->s2m);
   f(h->d_work); f(h->d_work_ptr);
+  f(h->d_tiles); f(h->d_state); f(h->d_flag); f(h->d_acc);
+  if (h->h_t) (void)hipHostFree(h->h_t);
   if (h->h_flags) (void)hipHostFree(h->h_flags);
   if (h->h_run) (void)hipHostFree(h->h_run);
   for (hipEvent_t e : h->ev_poll)
@@ -275,6 +290,24 @@ int build_work(hwenou_handle* h) {
   HIPCHK(hipMemcpy(h->d_work, items.data(), items.size() * sizeof(WorkItem),
                    hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(h->d_work_ptr, ptr.data(), ptr.size() * sizeof(int), hipMemcpyHostToDevice));
+  if (h->whole_steps) {
+    // waves of the whole-step launch, and its accumulators by the same rule
+    int w = h->waves_per_cu;
+    if (w <= 0) {
+      const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
+      w = kStepThreads / 64 * occupancy_step_1d(h->desc.eq, chr, h->mixed, kStepThreads);
+      if (w <= 0) w = 4;
+    }
+    h->step_waves = (int)std::min<long long>(h->n_tiles, (long long)h->n_cu * w);
+    int most = 0;
+    for (int k = 0; k < h->n_inst; ++k) {
+      const long long nt = (h->inst[k].nx + kStepWidth - 1) / kStepWidth;
+      most = std::max(most, (int)(nt * h->step_waves / h->n_tiles) + 1);
+    }
+    int slots = 1;
+    while (slots < kAlphaSlots && 64 * slots < most) slots *= 2;
+    h->step_slots = slots;
+  }
   h->work_dirty = false;
   return HWENOU_OK;
 }
@@ -366,6 +399,7 @@ AuxArgs aux_args(hwenou_handle* h, const double* u) {
   a.plane = h->plane;
   a.u = u;
   a.alpha = h->d_alpha;
+  a.alpha_stride = 2;
   a.dt = h->d_dt;
   a.t = h->d_t;
   a.steps = h->d_steps;
@@ -520,6 +554,32 @@ int hwenou_create(const hwenou_desc* d, int n_inst, const hwenou_inst* inst, voi
   TRY(dalloc(&h->s2u, u_count));
   TRY(dalloc_bytes(&h->s1m, mom_bytes));
   TRY(dalloc_bytes(&h->s2m, mom_bytes));
+  if (d->dim == 1) {
+    std::vector<TileItem> tiles;
+    h->whole_steps = true;
+    for (int k = 0; k < n_inst; ++k) {
+      if ((inst[k].bc[0] == HWENOU_BC_PERIODIC) != (inst[k].bc[1] == HWENOU_BC_PERIODIC))
+        h->whole_steps = false;
+      for (int s = 0; s < inst[k].nx; s += kStepWidth) tiles.push_back({k, s});
+    }
+    h->n_tiles = (int)tiles.size();
+    if (h->whole_steps) {
+      TRY(dalloc(&h->d_tiles, tiles.size()));
+      TRY(dalloc(&h->d_state, 2 * (size_t)n_inst));
+      TRY(dalloc(&h->d_flag, 2 * (size_t)n_inst));
+      TRY(dalloc(&h->d_acc, 4 * (size_t)kAlphaStride * kAlphaSlots * n_inst));
+      hipError_t et = hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(TileItem),
+                                hipMemcpyHostToDevice);
+      if (et == hipSuccess)
+        et = hipHostMalloc(reinterpret_cast<void**>(&h->h_t), n_inst * (sizeof(double) + 2 * sizeof(int)));
+      if (et != hipSuccess) {
+        free_handle(h);
+        return hip_fail(et, "hipMemcpy / hipHostMalloc");
+      }
+      h->h_steps = reinterpret_cast<int*>(h->h_t + n_inst);
+      h->h_status = h->h_steps + n_inst;
+    }
+  }
 #undef TRY
   auto chk = [&](hipError_t e2, const char* what) {
     if (e2 != hipSuccess) {
@@ -587,7 +647,7 @@ int hwenou_autotune(hwenou_handle* h, const double* ubar, const void* mom, int r
   HIPCHK(hipStreamWaitEvent(st, h->ev_in, 0));
   HIPCHK(hipMemsetAsync(h->d_dt, 0, h->n_inst * sizeof(double), st));
   AuxArgs a = aux_args(h, ubar);
-  hipError_t e = launch_max_wavespeed(a, st);
+  hipError_t e = launch_max_wavespeed(a, true, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   hipEvent_t t0, t1;
   HIPCHK(hipEventCreate(&t0));
@@ -642,7 +702,7 @@ int hwenou_max_wavespeed(hwenou_handle* h, const double* ubar, double* alpha_dev
     return HWENOU_EINVAL;
   AuxArgs a = aux_args(h, ubar);
   a.alpha = alpha_dev;
-  hipError_t e = launch_max_wavespeed(a, h->stream);
+  hipError_t e = launch_max_wavespeed(a, true, h->stream);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   return HWENOU_OK;
 }
@@ -679,6 +739,120 @@ int hwenou_inst_status(hwenou_handle* h, int* flags) {
 
 int hwenou_status(hwenou_handle* h) { return hwenou_inst_status(h, nullptr); }
 
+}  // extern "C"
+
+namespace {
+
+// hwenou_advance by whole steps, one launch each (step1d.hip), on the caller's
+// stream: a kernel that resets the run's state, the wave speed of the initial
+// averages, the steps, and a kernel that brings the results home.  The state
+// alternates between the caller's arrays and the stage buffers.
+int advance_whole_steps(hwenou_handle* h, double* ubar, void* mom, const RunParams& R,
+                        double* t_out, int* steps_out) {
+  hipStream_t st = h->stream;
+  const int n = h->n_inst;
+  const size_t lines = (size_t)kAlphaStride * kAlphaSlots * n;
+  RunArgs r;
+  r.R = R;
+  r.run = h->d_run;
+  r.n_inst = n;
+  r.slots = h->step_slots;
+  r.nc = r.mom_planes = h->nc;
+  r.mom_elem = (int)h->mom_elem;
+  for (int b = 0; b < 2; ++b) {
+    r.st[b] = h->d_state + (size_t)b * n;
+    r.flag[b] = h->d_flag + (size_t)b * n;
+  }
+  for (int b = 0; b < 4; ++b) r.acc[b] = h->d_acc + b * lines;
+  r.last = 0;
+  r.u_odd = h->s1u;
+  r.m_odd = h->s1m;
+  r.u = ubar;
+  r.m = mom;
+  r.inst = h->d_inst;
+  r.plane = h->plane;
+  r.tiles = h->d_tiles;
+  r.n_tiles = h->n_tiles;
+  r.status = h->d_status;
+  r.t_host = h->h_t;
+  r.steps_host = h->h_steps;
+  r.status_host = h->h_status;
+  r.running_host = h->h_flags;
+  hipError_t e = launch_run_begin(r, st);
+  if (e != hipSuccess) return hip_fail(e, "run_begin launch");
+  AuxArgs a = aux_args(h, ubar);
+  a.alpha = r.acc[0];
+  a.alpha_stride = kAlphaStride * h->step_slots;
+  a.status = r.flag[0];
+  e = launch_max_wavespeed(a, false, st);
+  if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
+
+  const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
+  const SchemeParams P = scheme_params(h->desc);
+  auto step = [&](auto* tag, int p) {  // the p-th step of the run
+    using TM = std::remove_pointer_t<decltype(tag)>;
+    StepArgs<TM> A;
+    A.P = P;
+    A.inst = h->d_inst;
+    A.run = h->d_run;
+    A.u_in = p & 1 ? h->s1u : ubar;
+    A.m_in = static_cast<const TM*>(p & 1 ? h->s1m : mom);
+    A.u_out = p & 1 ? ubar : h->s1u;
+    A.m_out = static_cast<TM*>(p & 1 ? mom : h->s1m);
+    A.st_in = r.st[p & 1];
+    A.st_out = r.st[(p + 1) & 1];
+    A.flag_in = r.flag[p & 1];
+    A.flag_out = r.flag[(p + 1) & 1];
+    A.acc_in = r.acc[p & 3];
+    A.acc_out = r.acc[(p + 1) & 3];
+    A.acc_zero = r.acc[(p + 2) & 3];
+    A.slots = h->step_slots;
+    A.plane = h->plane;
+    A.tiles = h->d_tiles;
+    A.n_tiles = h->n_tiles;
+    A.n_waves = h->step_waves;
+    return launch_step_1d(h->desc.eq, chr, h->mixed, &A, h->step_waves, kStepThreads, st);
+  };
+  // Chunks of growing length; between them the device writes to a pinned slot
+  // whether any instance still runs, and the host waits only for the answer of
+  // the chunk before, so the device never idles.
+  int launched = 0, chunk = 64, slot = 0, prev = -1;
+  while (launched < R.max_steps) {
+    const int k = std::min(chunk, R.max_steps - launched);
+    for (int q = 0; q < k && e == hipSuccess; ++q)
+      e = h->mixed ? step(static_cast<float*>(nullptr), launched + q)
+                   : step(static_cast<double*>(nullptr), launched + q);
+    if (e != hipSuccess) break;
+    launched += k;
+    if (launched == R.max_steps) break;
+    r.last = launched & 1;
+    r.running_host = h->h_flags + slot;
+    if ((e = launch_run_poll(r, st)) != hipSuccess) break;
+    if ((e = hipEventRecord(h->ev_poll[slot], st)) != hipSuccess) break;
+    if (prev >= 0) {
+      if ((e = hipEventSynchronize(h->ev_poll[prev])) != hipSuccess) break;
+      if (!h->h_flags[prev]) break;
+    }
+    prev = slot;
+    slot ^= 1;
+    chunk = std::min(2 * chunk, 512);
+  }
+  h->u_base = nullptr;
+  if (e != hipSuccess) return hip_fail(e, "step launch");
+  r.last = launched & 1;
+  if ((e = launch_run_end(r, st)) != hipSuccess) return hip_fail(e, "run_end launch");
+  HIPCHK(hipStreamSynchronize(st));
+  if (t_out) std::memcpy(t_out, h->h_t, n * sizeof(double));
+  if (steps_out) std::memcpy(steps_out, h->h_steps, n * sizeof(int));
+  for (int k = 0; k < n; ++k)
+    if (h->h_status[k] & 1) return HWENOU_ENONPHYSICAL;
+  return HWENOU_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
 int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double t_final,
                    int max_steps, double* t_out, int* steps_out) {
   if (!h || !ubar || !mom || !(cfl > 0.0) || !(t_final >= 0.0) || max_steps < 0)
@@ -688,6 +862,8 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
     int rc = build_work(h);
     if (rc) return rc;
   }
+  if (h->whole_steps)
+    return advance_whole_steps(h, ubar, mom, {cfl, t_final, max_steps}, t_out, steps_out);
   hipStream_t st = h->own;
   // order after the caller's prior work
   HIPCHK(hipEventRecord(h->ev_in, h->stream));
@@ -702,7 +878,7 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
   HIPCHK(hipMemsetAsync(h->d_done, 0, h->n_inst * sizeof(int), st));
   HIPCHK(hipMemsetAsync(h->d_status, 0, h->n_inst * sizeof(int), st));
   AuxArgs a = aux_args(h, ubar);
-  hipError_t e = launch_max_wavespeed(a, st);
+  hipError_t e = launch_max_wavespeed(a, true, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   // the first step's dt; later ones are set by the finish kernel of the step before
   e = launch_dt(a, st);

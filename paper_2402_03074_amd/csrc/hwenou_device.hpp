@@ -577,6 +577,26 @@ __device__ __forceinline__ double wave_max(double x) {
   return x;
 }
 
+// The same maximum by DPP moves within and across the rows of 16 lanes, valid
+// on lane 63: 6 dependent steps of register moves, where the shuffles above
+// are 12 dependent LDS-crossbar reads.  Lanes without a source read 0, which
+// a maximum of non-negative values ignores.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_max_dpp(double x) {
+  x = fmax(x, dpp_or_zero<0x111, 0xf>(x));  // row_shr:1, 2, 4, 8
+  x = fmax(x, dpp_or_zero<0x112, 0xf>(x));
+  x = fmax(x, dpp_or_zero<0x114, 0xf>(x));
+  x = fmax(x, dpp_or_zero<0x118, 0xf>(x));
+  x = fmax(x, dpp_or_zero<0x142, 0xa>(x));  // row_bcast:15 into rows 1 and 3
+  return fmax(x, dpp_or_zero<0x143, 0xc>(x));  // row_bcast:31 into rows 2 and 3
+}
+
 // atomic max for non-negative doubles through their IEEE bit patterns
 __device__ __forceinline__ void atomic_max_nonneg(double* addr, double v) {
   atomicMax(reinterpret_cast<unsigned long long*>(addr),

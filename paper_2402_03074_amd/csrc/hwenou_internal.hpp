@@ -42,6 +42,74 @@ __device__ __host__ __forceinline__ int alpha_slot(int inst, int wave, int slots
   return kAlphaStride * (inst * slots + (wave & (slots - 1)));
 }
 
+// Parameters of one hwenou_advance call, read by the time-step kernels from
+// device memory so that a captured step graph stays valid across calls.
+struct RunParams {
+  double cfl, t_final;
+  int max_steps;
+};
+
+// Whole steps in 1D (step1d.hip): a tile of kStepWidth owned cells, and an
+// instance's time, step count and completion.
+constexpr int kStepWidth = 54;
+struct TileItem {
+  int inst, start;
+};
+struct StepState {
+  double t;
+  int steps, done;
+};
+
+// What one step of an instance starts from: its time step and wave speed, or
+// that it is done.  It is when it has reached t_final or max_steps, or a
+// kernel has flagged one of its states as non-physical or non-finite (it
+// stops after the step that failed, and its t and step count say where), or
+// its wave speed is infinite (failed: to be flagged now).  The same rule as
+// set_step of the one-stage path.
+struct StepDt {
+  double dt, alpha;
+  bool done, failed;
+};
+__device__ __forceinline__ StepDt step_dt(const RunParams& R, double dx, const StepState& s,
+                                          int flag, double ax) {
+  StepDt r;
+  r.alpha = ax;
+  r.dt = 0.0;
+  r.failed = false;
+  r.done = s.done || flag || s.steps >= R.max_steps || s.t >= R.t_final * (1.0 - 1e-14);
+  if (r.done) return r;
+  if (!isfinite(ax)) {
+    r.done = r.failed = true;
+    return r;
+  }
+  // zero wave speed: every flux vanishes, the CFL bound is infinite
+  r.dt = ax == 0.0 ? R.t_final - s.t : R.cfl * dx / ax;
+  if (s.t + r.dt > R.t_final) r.dt = R.t_final - s.t;
+  return r;
+}
+
+template <class TM>
+struct StepArgs {
+  SchemeParams P;
+  const InstDev* inst;
+  const RunParams* run;
+  const double* u_in;
+  const TM* m_in;
+  double* u_out;
+  TM* m_out;
+  const StepState* st_in;  // [n_inst], written by the step before
+  StepState* st_out;
+  const int* flag_in;      // [n_inst]: non-physical states found before this step
+  int* flag_out;           // [n_inst]: ... and by this step
+  const double* acc_in;    // wave speeds of the input, [n_inst][slots][kAlphaStride]
+  double* acc_out;         // wave speeds of the output (cleared by the step before)
+  double* acc_zero;        // accumulators to clear for the next step
+  int slots;
+  long long plane;
+  const TileItem* tiles;
+  int n_tiles, n_waves;    // wave w takes tiles [n_tiles w / n_waves, n_tiles (w+1) / n_waves)
+};
+
 template <class TM>
 struct StageArgs {
   SchemeParams P;
@@ -89,12 +157,10 @@ hipError_t launch_stage_2d(int eq, int char_mode, bool mixed, bool scale_invaria
 int occupancy_stage_1d(int eq, int char_mode, bool mixed, int threads);
 int occupancy_stage_2d(int eq, int char_mode, bool mixed, bool scale_invariant, int threads);
 
-// Parameters of one hwenou_advance call, read by the time-step kernels from
-// device memory so that a captured step graph stays valid across calls.
-struct RunParams {
-  double cfl, t_final;
-  int max_steps;
-};
+// whole Runge-Kutta steps in 1D, one per launch; args: StepArgs<float or double>
+hipError_t launch_step_1d(int eq, int char_mode, bool mixed, const void* args, int waves,
+                          int threads, hipStream_t s);
+int occupancy_step_1d(int eq, int char_mode, bool mixed, int threads);
 
 // auxiliary kernels
 struct AuxArgs {
@@ -103,7 +169,8 @@ struct AuxArgs {
   const InstDev* inst;
   long long plane;
   const double* u;       // [nc][plane]
-  double* alpha;         // [n_inst][2]
+  double* alpha;         // [n_inst][alpha_stride]: x and y wave speed first
+  int alpha_stride;
   double* dt;            // [n_inst]
   double* t;             // [n_inst]
   int* steps;            // [n_inst]
@@ -114,8 +181,35 @@ struct AuxArgs {
   const RunParams* run;  // CFL number, final time, step limit
   int* all_done;         // 1 when every instance is done
 };
-hipError_t launch_max_wavespeed(const AuxArgs& a, hipStream_t s);
+// a.alpha must be zero on entry unless `zero` asks for it to be cleared first
+hipError_t launch_max_wavespeed(const AuxArgs& a, bool zero, hipStream_t s);
 hipError_t launch_dt(const AuxArgs& a, hipStream_t s);
 hipError_t launch_finish(const AuxArgs& a, hipStream_t s);
+
+// Start and end of a run of whole 1D steps.
+struct RunArgs {
+  RunParams R;
+  RunParams* run;          // device copy of R
+  int n_inst, slots, nc, mom_planes, mom_elem;
+  StepState* st[2];
+  int* flag[2];
+  double* acc[4];
+  int last;                // buffer (0, 1) the last step wrote
+  // end of the run
+  const double* u_odd;     // scratch state that odd steps write
+  const void* m_odd;
+  double* u;
+  void* m;
+  const InstDev* inst;
+  long long plane;
+  const TileItem* tiles;
+  int n_tiles;
+  int* status;             // [n_inst] device status flags
+  double* t_host;          // pinned host results
+  int *steps_host, *status_host, *running_host;
+};
+hipError_t launch_run_begin(const RunArgs& a, hipStream_t s);
+hipError_t launch_run_poll(const RunArgs& a, hipStream_t s);
+hipError_t launch_run_end(const RunArgs& a, hipStream_t s);
 
 }  // namespace hwenou

@@ -1,0 +1,102 @@
+"""Whole 1D Runge-Kutta steps in one launch against one stage per launch.
+
+hwenou_advance runs 1D instances by whole steps (a wave keeps a tile's cells
+through the three stages and recomputes or images the cells around it);
+hwenou_stage runs one stage per launch.  Both evaluate the same expressions
+on the same values, so they agree bitwise, at the edges of the tiles, on
+grids smaller than a stencil's reach and at every boundary."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2402_03074_amd as H
+
+from gpu_util import to_gpu
+
+pytestmark = pytest.mark.gpu
+
+# one tile holds 54 cells, one launch's waves see 5 cells beyond it
+SIZES = [3, 4, 5, 7, 53, 54, 55, 57, 58, 59, 60, 107, 108, 109, 113, 200, 3001]
+SIDES = [("periodic", "periodic"), ("transmissive", "transmissive"),
+         ("reflective", "reflective"), ("reflective", "transmissive"),
+         ("periodic", "transmissive")]  # the last takes one stage per launch
+
+
+def _data(eq, n, seed):
+    rng = np.random.default_rng(seed)
+    nc = 3 if eq == "euler" else 1
+    if eq == "euler":
+        rho, v, p = rng.uniform(0.5, 1.0, n), rng.uniform(-0.3, 0.3, n), rng.uniform(0.5, 1.0, n)
+        u = np.stack([rho, rho * v, p / 0.4 + 0.5 * rho * v * v])
+    else:
+        u = rng.uniform(-0.5, 1.0, (1, n))
+    m = 0.02 * rng.uniform(-1, 1, (1, nc, n))
+    return u, m
+
+
+def _eager(S, insts, u, m, cfl, steps):
+    """The caller's own loop over the stages, on the state arrays themselves."""
+    s1, s2 = S.empty_state(), S.empty_state()
+    h = np.array([(I.x1 - I.x0) / I.nx for I in insts])
+    t = np.zeros(len(insts))
+    for _ in range(steps):
+        alpha = S.max_wavespeed(u)
+        a = alpha.cpu().numpy()[:, 0]
+        dt = cfl * h / a
+        t += dt
+        dtg = torch.tensor(dt, dtype=torch.float64, device="cuda")
+        S.stage(0, dtg, alpha, u, m, *s1)
+        S.stage(1, dtg, alpha, *s1, *s2)
+        S.stage(2, dtg, alpha, *s2, u, m)
+    return t
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("eq,char", [("advection", 0), ("burgers", 0), ("euler", 0), ("euler", 1)])
+@pytest.mark.parametrize("sides", SIDES, ids="-".join)
+def test_whole_steps_equal_stages(sides, eq, char, precision):
+    if eq != "euler" and "reflective" in sides:
+        pytest.skip("walls are defined for the Euler equations")
+    print(f"[gpu] whole steps {sides} {eq} {char} {precision}", flush=True)
+    for steps in (1, 2, 3):  # odd counts bring the state back from the scratch buffers
+        off, insts, us, ms = 0, [], [], []
+        for k, n in enumerate(SIZES):
+            insts.append(H.make_inst(n, 1, (0.0, 1.0), sides, offset=off))
+            u, m = _data(eq, n, 100 * k + steps)
+            us.append(u)
+            ms.append(m)
+            off += n
+        S = H.Solver(1, eq, insts, precision=precision, char_decomp=char, adv=(1.0, 0.0))
+        u0, m0 = np.concatenate(us, 1), np.concatenate(ms, 2)
+        ua, ma = to_gpu(u0), to_gpu(m0, S.mom_dtype)
+        ub, mb = to_gpu(u0), to_gpu(m0, S.mom_dtype)
+        t, n_steps = S.advance(ua, ma, 0.3, 1e30, steps)
+        te = _eager(S, insts, ub, mb, 0.3, steps)
+        assert n_steps == [steps] * len(SIZES) and np.array_equal(np.array(t), te)
+        assert torch.equal(ua, ub) and torch.equal(ma, mb)
+        S.close()
+
+
+def test_instances_stop_after_odd_and_even_steps():
+    """Instances that reach t_final after different step counts: each ends in
+    the caller's arrays, as it does alone."""
+    insts, us, ms, off = [], [], [], 0
+    for k, n in enumerate([40, 61, 90, 333, 700]):
+        u, m = _data("euler", n, 7 + k)
+        insts.append(H.make_inst(n, 1, (0.0, 1.0), "periodic", offset=off))
+        us.append(u)
+        ms.append(m)
+        off += n
+    S = H.Solver(1, "euler", insts)
+    ug, mg = to_gpu(np.concatenate(us, 1)), to_gpu(np.concatenate(ms, 2))
+    t, steps = S.advance(ug, mg, 0.4, 0.02, 1000)
+    S.close()
+    assert len(set(s % 2 for s in steps)) == 2, steps
+    for k, I in enumerate(insts):
+        S1 = H.Solver(1, "euler", [H.make_inst(I.nx, 1, (0.0, 1.0), "periodic")])
+        u1, m1 = to_gpu(us[k]), to_gpu(ms[k])
+        t1, s1 = S1.advance(u1, m1, 0.4, 0.02, 1000)
+        S1.close()
+        assert (t1[0], s1[0]) == (t[k], steps[k])
+        sl = slice(I.offset, I.offset + I.nx)
+        assert torch.equal(u1, ug[:, sl]) and torch.equal(m1, mg[:, :, sl])
