@@ -217,8 +217,18 @@ int build_work(hwenou_handle* h) {
     // strips read their shared columns at the same time.
     const int ny = h->inst[0].ny;
     const int ns = (h->inst[0].nx + kStripWidth - 1) / kStripWidth;
-    long long q = std::max<long long>(1, target_waves / ns);
-    q = std::min<long long>(q, std::max(1, ny / 4));  // at least 4 rows per run
+    // The fewest rows per run that keep the runs within the resident waves, down
+    // to one: a wave's time is that of its rows plus about 1.5 more (its two
+    // boundary rows run the y-sweep, and the LDS ring is filled first), so a
+    // grid too small to fill the SIMDs is fastest cut as short as it goes, and
+    // no shorter than its longest run (400 x 300, component-wise: 107 us per
+    // step in 100 runs of 3 rows per strip, 112 in 146 runs of 2 or 3).
+    // Against runs of at least 4 rows, per Runge-Kutta step: 131 x 97 cells
+    // (Euler, FP64) 204 -> 93 us, 240 x 240 (Burgers) 46 -> 34 us, 500 x 333
+    // (Euler, per-interface bases) 433 -> 320 us.
+    const long long fit = std::min<long long>(std::max<long long>(1, target_waves / ns), ny);
+    const long long rows = (ny + fit - 1) / fit;
+    const long long q = (ny + rows - 1) / rows;
     ptr.push_back(0);
     for (long long b = 0; b < q; ++b) {
       const int r0 = (int)(ny * b / q), r1 = (int)(ny * (b + 1) / q);
@@ -241,9 +251,10 @@ int build_work(hwenou_handle* h) {
         total += h->inst[k].ny;
       }
     }
-    long long per = h->rows_per_item > 0 ? h->rows_per_item
-                                         : (total + target_waves - 1) / target_waves;
-    per = std::max<long long>(per, 4);
+    // (a given shape has at least 4 rows per run)
+    const long long per = h->rows_per_item > 0
+                              ? std::max(h->rows_per_item, 4)
+                              : std::max<long long>(1, (total + target_waves - 1) / target_waves);
     ptr.push_back(0);
     long long used = 0;  // rows assigned to the current wave
     for (const Strip& s : strips) {

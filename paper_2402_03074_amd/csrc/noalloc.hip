@@ -69,10 +69,9 @@ constexpr size_t kOffPtr = 512;       // int work_ptr[n_waves + 1]
 // Writes the instance record, clears the status word, and builds the work
 // lists of one instance by formula (the same decomposition as the handle's
 // lists: 1D, 62-cell tiles dealt out in contiguous runs; 2D, every strip of
-// 62 columns cut into chunks of `per` rows, one chunk per wave).
+// 62 columns cut at the same rows into `chunks` runs, one per wave).
 __global__ void noalloc_setup_kernel(unsigned char* base, InstDev I, int dim, int n_items,
-                                     int n_waves, int per, int chunks, size_t off_items,
-                                     int use_status) {
+                                     int n_waves, int chunks, size_t off_items, int use_status) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t == 0) {
     *reinterpret_cast<InstDev*>(base + kOffInst) = I;
@@ -86,7 +85,8 @@ __global__ void noalloc_setup_kernel(unsigned char* base, InstDev I, int dim, in
   } else {
     if (t < n_items) {
       const int s = t / chunks, c = t % chunks;
-      const int r0 = c * per, r1 = min(r0 + per, I.ny);
+      const int r0 = (int)((long long)I.ny * c / chunks);
+      const int r1 = (int)((long long)I.ny * (c + 1) / chunks);
       items[t] = {0, s, r0, r1};
     }
     if (t <= n_waves) ptr[t] = t;  // one item per wave
@@ -135,14 +135,17 @@ extern "C" int hwenou_step_noalloc(const hwenou_desc* d, const hwenou_inst* inst
                      : occupancy_stage_2d(d->eq, chr, mixed, si, 64);
   if (wpc <= 0) wpc = 4;
   const long long target = (long long)di->n_cu * wpc;
-  int n_items, n_waves, per = 0, chunks = 0;
+  int n_items, n_waves, chunks = 0;
   if (dim == 1) {
     n_items = (int)((cells + kStripWidth - 1) / kStripWidth);
     n_waves = (int)std::min<long long>(n_items, target);
   } else {
     const int ns = (nx + kStripWidth - 1) / kStripWidth;
-    per = (int)std::max<long long>(4, ((long long)ns * ny + target - 1) / target);
-    chunks = (ny + per - 1) / per;
+    // the fewest rows per run that keep the runs within the resident waves, down
+    // to one, as in the handle's lists for one grid
+    const int fit = (int)std::min<long long>(std::max<long long>(1, target / ns), ny);
+    const int rows = (ny + fit - 1) / fit;
+    chunks = (ny + rows - 1) / rows;
     n_items = ns * chunks;
     n_waves = n_items;
   }
@@ -161,7 +164,7 @@ extern "C" int hwenou_step_noalloc(const hwenou_desc* d, const hwenou_inst* inst
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int setup_threads = std::max(n_items, n_waves + 1);
   hipLaunchKernelGGL(noalloc_setup_kernel, dim3((setup_threads + 255) / 256), dim3(256), 0, st,
-                     base, inst_dev(d, *inst), dim, n_items, n_waves, per, chunks, off_items,
+                     base, inst_dev(d, *inst), dim, n_items, n_waves, chunks, off_items,
                      status_dev ? 0 : 1);
   if ((e = hipGetLastError()) != hipSuccess) return HWENOU_EHIP;
 
