@@ -304,33 +304,67 @@ struct Sten2 {
   double w[4];
 };
 
+// TR = double forms sums and differences of opposite cells first (64 operations
+// instead of 75).  The mixed form keeps the order its results were established
+// with: a different FP64 rounding here flips FP32 roundings behind it, which
+// moves single averages by 1e-7.
+template <class TR>
 __device__ __forceinline__ void p0_coeffs_2d(const Sten2& s, double (&c)[15]) {
   const double u1 = s.u[0], u2 = s.u[1], u3 = s.u[2], u4 = s.u[3], u5 = s.u[4], u6 = s.u[5],
                u7 = s.u[6], u8 = s.u[7], u9 = s.u[8];
   const double v2 = s.v[0], v4 = s.v[1], v6 = s.v[2], v8 = s.v[3];
   const double w2 = s.w[0], w4 = s.w[1], w6 = s.w[2], w8 = s.w[3];
-  const double corner = u1 + u3 + u7 + u9;
-  const double ux = -u1 + u3 - u7 + u9;  // x-odd corner combination
-  const double uy = -u1 - u3 + u7 + u9;  // y-odd corner combination
-  const double uxy = u1 - u3 - u7 + u9;  // xy-odd corner combination
-  c[0] = (1.0 / 576.0) * corner - (133.0 / 1152.0) * (u2 + u4 + u6 + u8) + (419.0 / 288.0) * u5 +
-         (27.0 / 64.0) * (v6 - v4) + (27.0 / 64.0) * (w8 - w2);
-  c[1] = (-1.0 / 48.0) * ux + (397.0 / 456.0) * (u6 - u4) - (75.0 / 19.0) * (v4 + v6);
-  c[2] = (-1.0 / 48.0) * uy + (397.0 / 456.0) * (u8 - u2) - (75.0 / 19.0) * (w2 + w8);
-  c[3] = (-1.0 / 48.0) * corner + (1.0 / 24.0) * (u2 + u8) + (71.0 / 48.0) * (u4 + u6) -
-         (71.0 / 24.0) * u5 + (45.0 / 8.0) * (v4 - v6);
-  c[4] = (-7.0 / 22.0) * uxy + (75.0 / 11.0) * (v8 - v2) + (75.0 / 11.0) * (w6 - w4);
-  c[5] = (-1.0 / 48.0) * corner + (71.0 / 48.0) * (u2 + u8) + (1.0 / 24.0) * (u4 + u6) -
-         (71.0 / 24.0) * u5 + (45.0 / 8.0) * (w2 - w8);
-  c[6] = (5.0 / 19.0) * (u4 - u6) + (60.0 / 19.0) * (v4 + v6);
-  c[7] = 0.25 * uy + 0.5 * (u2 - u8);
-  c[8] = 0.25 * ux + 0.5 * (u4 - u6);
-  c[9] = (5.0 / 19.0) * (u2 - u8) + (60.0 / 19.0) * (w2 + w8);
-  c[10] = (-5.0 / 8.0) * (u4 + u6) + 1.25 * u5 + (15.0 / 4.0) * (v6 - v4);
-  c[11] = (5.0 / 22.0) * uxy + (60.0 / 11.0) * (v2 - v8);
-  c[12] = 0.25 * corner - 0.5 * (u2 + u4 + u6 + u8) + u5;
-  c[13] = (5.0 / 22.0) * uxy + (60.0 / 11.0) * (w4 - w6);
-  c[14] = (-5.0 / 8.0) * (u2 + u8) + 1.25 * u5 + (15.0 / 4.0) * (w8 - w2);
+  if constexpr (sizeof(TR) == 8) {
+    // sums and differences of opposite cells first: every coefficient is a
+    // combination of one parity
+    const double s19 = u1 + u9, s37 = u3 + u7, d19 = u9 - u1, d37 = u3 - u7;
+    const double corner = s19 + s37, uxy = s19 - s37;  // even, and xy-odd, corner combinations
+    const double ux = d19 + d37, uy = d19 - d37;       // x-odd and y-odd corner combinations
+    const double sx = u4 + u6, dx = u6 - u4, sy = u2 + u8, dy = u8 - u2, sxy = sx + sy;
+    const double sv = v4 + v6, dv = v6 - v4, cv = v8 - v2;
+    const double sw = w2 + w8, dw = w8 - w2, cw = w6 - w4;
+    c[0] = (1.0 / 576.0) * corner - (133.0 / 1152.0) * sxy + (419.0 / 288.0) * u5 +
+           (27.0 / 64.0) * (dv + dw);
+    c[1] = (-1.0 / 48.0) * ux + (397.0 / 456.0) * dx - (75.0 / 19.0) * sv;
+    c[2] = (-1.0 / 48.0) * uy + (397.0 / 456.0) * dy - (75.0 / 19.0) * sw;
+    c[3] = (-1.0 / 48.0) * corner + (1.0 / 24.0) * sy + (71.0 / 48.0) * sx - (71.0 / 24.0) * u5 -
+           (45.0 / 8.0) * dv;
+    c[4] = (-7.0 / 22.0) * uxy + (75.0 / 11.0) * (cv + cw);
+    c[5] = (-1.0 / 48.0) * corner + (71.0 / 48.0) * sy + (1.0 / 24.0) * sx - (71.0 / 24.0) * u5 -
+           (45.0 / 8.0) * dw;
+    c[6] = (-5.0 / 19.0) * dx + (60.0 / 19.0) * sv;
+    c[7] = 0.25 * uy - 0.5 * dy;
+    c[8] = 0.25 * ux - 0.5 * dx;
+    c[9] = (-5.0 / 19.0) * dy + (60.0 / 19.0) * sw;
+    c[10] = (-5.0 / 8.0) * sx + 1.25 * u5 + (15.0 / 4.0) * dv;
+    c[11] = (5.0 / 22.0) * uxy - (60.0 / 11.0) * cv;
+    c[12] = 0.25 * corner - 0.5 * sxy + u5;
+    c[13] = (5.0 / 22.0) * uxy - (60.0 / 11.0) * cw;
+    c[14] = (-5.0 / 8.0) * sy + 1.25 * u5 + (15.0 / 4.0) * dw;
+  } else {
+    const double corner = u1 + u3 + u7 + u9;
+    const double ux = -u1 + u3 - u7 + u9;  // x-odd corner combination
+    const double uy = -u1 - u3 + u7 + u9;  // y-odd corner combination
+    const double uxy = u1 - u3 - u7 + u9;  // xy-odd corner combination
+    c[0] = (1.0 / 576.0) * corner - (133.0 / 1152.0) * (u2 + u4 + u6 + u8) + (419.0 / 288.0) * u5 +
+           (27.0 / 64.0) * (v6 - v4) + (27.0 / 64.0) * (w8 - w2);
+    c[1] = (-1.0 / 48.0) * ux + (397.0 / 456.0) * (u6 - u4) - (75.0 / 19.0) * (v4 + v6);
+    c[2] = (-1.0 / 48.0) * uy + (397.0 / 456.0) * (u8 - u2) - (75.0 / 19.0) * (w2 + w8);
+    c[3] = (-1.0 / 48.0) * corner + (1.0 / 24.0) * (u2 + u8) + (71.0 / 48.0) * (u4 + u6) -
+           (71.0 / 24.0) * u5 + (45.0 / 8.0) * (v4 - v6);
+    c[4] = (-7.0 / 22.0) * uxy + (75.0 / 11.0) * (v8 - v2) + (75.0 / 11.0) * (w6 - w4);
+    c[5] = (-1.0 / 48.0) * corner + (71.0 / 48.0) * (u2 + u8) + (1.0 / 24.0) * (u4 + u6) -
+           (71.0 / 24.0) * u5 + (45.0 / 8.0) * (w2 - w8);
+    c[6] = (5.0 / 19.0) * (u4 - u6) + (60.0 / 19.0) * (v4 + v6);
+    c[7] = 0.25 * uy + 0.5 * (u2 - u8);
+    c[8] = 0.25 * ux + 0.5 * (u4 - u6);
+    c[9] = (5.0 / 19.0) * (u2 - u8) + (60.0 / 19.0) * (w2 + w8);
+    c[10] = (-5.0 / 8.0) * (u4 + u6) + 1.25 * u5 + (15.0 / 4.0) * (v6 - v4);
+    c[11] = (5.0 / 22.0) * uxy + (60.0 / 11.0) * (v2 - v8);
+    c[12] = 0.25 * corner - 0.5 * (u2 + u4 + u6 + u8) + u5;
+    c[13] = (5.0 / 22.0) * uxy + (60.0 / 11.0) * (w4 - w6);
+    c[14] = (-5.0 / 8.0) * (u2 + u8) + 1.25 * u5 + (15.0 / 4.0) * (w8 - w2);
+  }
 }
 
 __device__ __forceinline__ double sq(double x) { return x * x; }

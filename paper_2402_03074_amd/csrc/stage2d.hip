@@ -85,49 +85,31 @@ __device__ __forceinline__ Prim make_prim_roe(double gm1, const double (&UL)[4],
   return p;
 }
 
-// Row k of the left eigenvectors and column k of the right eigenvectors of
-// the Euler flux Jacobian in direction DIR (ideal gas):
+// Row k of the left eigenvectors of the Euler flux Jacobian in direction DIR
+// (ideal gas), normalised to the right eigenvectors
 // x: R = [(1,u-c,v,H-uc), (1,u,v,q^2/2), (0,0,1,v), (1,u+c,v,H+uc)]
 // y: R = [(1,u,v-c,H-vc), (1,u,v,q^2/2), (0,1,0,u), (1,u,v+c,H+vc)]
 template <int DIR>
-__device__ __forceinline__ void eig_row(const Prim& p, int k, double (&l)[4], double (&r)[4]) {
+__device__ __forceinline__ void eig_row(const Prim& p, int k, double (&l)[4]) {
   const double un = DIR == 0 ? p.u : p.v;  // normal velocity
   const double ut = DIR == 0 ? p.v : p.u;  // tangential velocity
-  const int n = DIR == 0 ? 1 : 2, t = DIR == 0 ? 2 : 1;
-  double ll[4], rr[4];
+  constexpr int n = DIR == 0 ? 1 : 2, t = DIR == 0 ? 2 : 1;
   if (k == 0 || k == 3) {
     const double s = k == 0 ? 1.0 : -1.0;
-    ll[0] = 0.5 * (p.b2 + s * un * p.ci);
-    ll[n] = -0.5 * (p.b1 * un + s * p.ci);
-    ll[t] = -0.5 * p.b1 * ut;
-    ll[3] = 0.5 * p.b1;
-    rr[0] = 1.0;
-    rr[n] = un - s * p.c;
-    rr[t] = ut;
-    rr[3] = p.H - s * un * p.c;
+    l[0] = 0.5 * (p.b2 + s * un * p.ci);
+    l[n] = -0.5 * (p.b1 * un + s * p.ci);
+    l[t] = -0.5 * p.b1 * ut;
+    l[3] = 0.5 * p.b1;
   } else if (k == 1) {
-    ll[0] = 1.0 - p.b2;
-    ll[n] = p.b1 * un;
-    ll[t] = p.b1 * ut;
-    ll[3] = -p.b1;
-    rr[0] = 1.0;
-    rr[n] = un;
-    rr[t] = ut;
-    rr[3] = 0.5 * p.q2;
+    l[0] = 1.0 - p.b2;
+    l[n] = p.b1 * un;
+    l[t] = p.b1 * ut;
+    l[3] = -p.b1;
   } else {
-    ll[0] = -ut;
-    ll[n] = 0.0;
-    ll[t] = 1.0;
-    ll[3] = 0.0;
-    rr[0] = 0.0;
-    rr[n] = 0.0;
-    rr[t] = 1.0;
-    rr[3] = ut;
-  }
-#pragma unroll
-  for (int m = 0; m < 4; ++m) {
-    l[m] = ll[m];
-    r[m] = rr[m];
+    l[0] = -ut;
+    l[n] = 0.0;
+    l[t] = 1.0;
+    l[3] = 0.0;
   }
 }
 
@@ -158,19 +140,64 @@ __device__ __forceinline__ void read_stencil(const RowBuf<NC, TM>& B, int sb, in
   S.w[3] = B.m[st][1][k][l + 1];
 }
 
-// Scalar HWENO reconstruction of one stencil -> combined coefficients
+// What the reconstruction of one scalar field needs of its stencil, linear in
+// it: the coefficients of p0 and the values at cells 2, 4, 5, 6, 8.
+struct Field {
+  double c[15], x[5];
+};
+
+template <class TR>
+__device__ __forceinline__ void make_field(const Sten2& S, Field& F) {
+  p0_coeffs_2d<TR>(S, F.c);
+  F.x[0] = S.u[1];
+  F.x[1] = S.u[3];
+  F.x[2] = S.u[4];
+  F.x[3] = S.u[5];
+  F.x[4] = S.u[7];
+}
+
+// F = A + s B
+__device__ __forceinline__ void add_fields(const Field& A, double s, const Field& B, Field& F) {
+#pragma unroll
+  for (int n = 0; n < 15; ++n) F.c[n] = fma(s, B.c[n], A.c[n]);
+#pragma unroll
+  for (int n = 0; n < 5; ++n) F.x[n] = fma(s, B.x[n], A.x[n]);
+}
+
+// Scalar HWENO reconstruction of one field -> combined coefficients
 template <class TR, bool SI, bool FOLD = false>
-__device__ __forceinline__ void recon_scalar(const SchemeParams& P, const Sten2& S, TR (&C)[15],
-                                             double* a_out = nullptr) {
-  double c[15];
-  p0_coeffs_2d(S, c);
-  const double u5 = S.u[4];
-  const double asum = fabs(S.u[1]) + fabs(S.u[3]) + fabs(u5) + fabs(S.u[5]) + fabs(S.u[7]);
-  hweno_2d<TR, SI, FOLD>(P, c, u5, u5 - S.u[3], S.u[5] - u5, u5 - S.u[1], S.u[7] - u5, asum, C,
+__device__ __forceinline__ void recon_field(const SchemeParams& P, const Field& F, TR (&C)[15],
+                                            double* a_out = nullptr) {
+  const double u5 = F.x[2];
+  const double asum = fabs(F.x[0]) + fabs(F.x[1]) + fabs(u5) + fabs(F.x[3]) + fabs(F.x[4]);
+  hweno_2d<TR, SI, FOLD>(P, F.c, u5, u5 - F.x[1], F.x[3] - u5, u5 - F.x[0], F.x[4] - u5, asum, C,
                          a_out);
 }
 
-// One characteristic field K of the sweep in direction DIR: project the
+// S += s * (stencil of component k); first = true: S = s * (...)
+template <bool FIRST, int NC, class TM>
+__device__ __forceinline__ void add_stencil(double s, const Sten2& A, Sten2& S) {
+#pragma unroll
+  for (int q = 0; q < 9; ++q) S.u[q] = FIRST ? s * A.u[q] : fma(s, A.u[q], S.u[q]);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    S.v[q] = FIRST ? s * A.v[q] : fma(s, A.v[q], S.v[q]);
+    S.w[q] = FIRST ? s * A.w[q] : fma(s, A.w[q], S.w[q]);
+  }
+}
+
+// Stencil of (component k) - s (density): the momentum relative to velocity s.
+template <class TR, class TM>
+__device__ __forceinline__ void relative_momentum(const RowBuf<4, TM>& B, int sb, int sc, int st,
+                                                  int l, int k, double s, Field& F) {
+  Sten2 R, M;
+  read_stencil<4, TM>(B, sb, sc, st, l, 0, R);
+  read_stencil<4, TM>(B, sb, sc, st, l, k, M);
+  add_stencil<false, 4, TM>(-s, R, M);
+  make_field<TR>(M, F);
+}
+
+// One characteristic field K of the sweep in direction DIR, mixed form: project the
 // stencil with row K of L and reconstruct.  Returns C (C[0..2] combined
 // coefficients, C[3..14] p0 coefficients) and the factor a of p0.  The shear
 // field (K = 2) has only two non-zero entries in its L row; they are used
@@ -179,8 +206,8 @@ template <int DIR, int K, bool SI, class TR, class TM>
 __device__ __forceinline__ void char_field(const SchemeParams& P, const Prim& pr,
                                            const RowBuf<4, TM>& B, int sb, int sc, int st, int l,
                                            TR (&C)[15], double& a) {
-  double lrow[4], rcol[4];
-  eig_row<DIR>(pr, K, lrow, rcol);
+  double lrow[4];
+  eig_row<DIR>(pr, K, lrow);
   Sten2 W;
   if constexpr (K == 2) {
     // L row: -u_t at density, 1 at the tangential momentum
@@ -215,13 +242,36 @@ __device__ __forceinline__ void char_field(const SchemeParams& P, const Prim& pr
       }
     }
   }
-  recon_scalar<TR, SI, true>(P, W, C, &a);
+  Field F;
+  make_field<TR>(W, F);
+  recon_field<TR, SI, true>(P, F, C, &a);
 }
 
 // Characteristic sweep in direction DIR: combined polynomials of the four
 // fields mapped back to conserved variables, Cc[m][n] = sum_K R[m][K] P_K[n].
-// Each field's polynomial P_K arrives as C with C[0..2] combined and C[3..14]
-// still to be scaled by the factor a of its p0.  The right eigenvectors
+//
+// Projection, FP64 form.  The left eigenvectors of the flux Jacobian are
+//   l0 = P - N / (2c),  l1 = rho - 2 P,  l2 = T,  l3 = P + N / (2c)
+// of the fields
+//   P = (b2 rho - b1 (u m_x + v m_y - E)) / 2,
+//   N = m_n - u_n rho,  T = m_t - u_t rho
+// (normal and tangential momentum relative to the cell's velocity).  The
+// coefficients of p0 are linear in the stencil, so they are formed for P, N, T
+// and the density and combined; P does not depend on the direction and goes
+// from the first sweep to the second through LDS (PARKP).  Per cell and both
+// directions that is about 620 operations and 190 LDS reads of stencil values,
+// where projecting each of the seven field-sweeps and forming its p0 takes 930
+// and 270.  2048^2 grid: 2.20 -> 2.13 ms per Runge-Kutta step; 500 x 333 with
+// per-interface bases: 320 -> 293 us.
+// The mixed form projects field by field (char_field): its FP32 results are
+// bound to the FP64 rounding in front of them (see p0_coeffs_2d).
+// The entropy field (K = 1) has the same left row and right column in both
+// directions: its polynomial is reconstructed once per cell, by the first
+// sweep, and passed on through LDS (PARK: a second sweep follows).
+//
+// Mapping back.  Each field's polynomial P_K arrives as C with C[0..2]
+// combined and C[3..14] still to be scaled by the factor a of its p0.  The
+// right eigenvectors
 //   r0 = (1, un - c, ut, H - un c), r1 = (1, un, ut, q^2/2),
 //   r2 = (0, 0, 1, ut),             r3 = (1, un + c, ut, H + un c)
 // (components: density, normal momentum, tangential momentum, energy) give
@@ -230,35 +280,76 @@ __device__ __forceinline__ void char_field(const SchemeParams& P, const Prim& pr
 //   Cc_t   = ut Cc_rho + P2,
 //   Cc_E   = H S + un c D + q^2/2 P1 + ut P2,
 // so the fields are taken in the order 0, 3, 1, 2 and fold into S, D and
-// then into Cc.  The entropy field (K = 1) has the same left row and right
-// column in both directions: its polynomial is reconstructed once per cell
-// (by the first sweep) and passed to the second through LDS (PARK: a second
-// sweep follows).  OVERLAP12: no scheduling barrier between fields 1 and 2
+// then into Cc.  OVERLAP12: no scheduling barrier between fields 1 and 2
 // (the FP64 split sweeps fit their registers without it and run 0.7% faster;
 // the other kernels then spill or run slower).
-template <int DIR, bool SI, bool PARK, class TR, class TM, bool OVERLAP12 = false>
+template <int DIR, bool SI, bool PARK, bool PARKP, class TR, class TM, bool OVERLAP12 = false>
 __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr,
                                            const RowBuf<4, TM>& B, int sb, int sc, int st, int l,
-                                           TR (&Cc)[4][15], TR (*c1buf)[64], bool have_c1) {
+                                           TR (&Cc)[4][15], TR (*c1buf)[64], double (*pbuf)[64],
+                                           bool have_c1) {
   constexpr int nd = DIR == 0 ? 1 : 2, td = DIR == 0 ? 2 : 1;  // normal, tangential momentum
   const double un = DIR == 0 ? pr.u : pr.v, ut = DIR == 0 ? pr.v : pr.u;
+  constexpr bool FIELDS = sizeof(TR) == 8;
   TR C[15], S[15], D[15];
   double a;
-  char_field<DIR, 0, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
+  Field FP;
   {
-    const TR a0 = (TR)a;
+    Field FN, F;
+    const double hc = 0.5 * pr.ci;
+    if constexpr (!FIELDS) {
+      char_field<DIR, 0, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
+    } else if (!(PARKP && have_c1)) {
+      Sten2 A, WP, WN;
+      const double hb = 0.5 * pr.b1;
+      read_stencil<4, TM>(B, sb, sc, st, l, 0, A);
+      add_stencil<true, 4, TM>(0.5 * pr.b2, A, WP);
+      read_stencil<4, TM>(B, sb, sc, st, l, nd, WN);
+      add_stencil<false, 4, TM>(-hb * un, WN, WP);
+      add_stencil<false, 4, TM>(-un, A, WN);
+      read_stencil<4, TM>(B, sb, sc, st, l, td, A);
+      add_stencil<false, 4, TM>(-hb * ut, A, WP);
+      read_stencil<4, TM>(B, sb, sc, st, l, 3, A);
+      add_stencil<false, 4, TM>(hb, A, WP);
+      make_field<TR>(WP, FP);
+      make_field<TR>(WN, FN);
+      if constexpr (PARKP) {
 #pragma unroll
-    for (int n = 0; n < 15; ++n) S[n] = n < 3 ? C[n] : a0 * C[n];  // P0
-  }
-  char_field<DIR, 3, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
-  {
-    const TR a3 = (TR)a;
+        for (int n = 0; n < 15; ++n) pbuf[n][l] = FP.c[n];
 #pragma unroll
-    for (int n = 0; n < 15; ++n) {
-      const TR p0 = S[n];
-      const TR f = n < 3 ? (TR)1 : a3;
-      S[n] = f * C[n] + p0;
-      D[n] = f * C[n] - p0;
+        for (int n = 0; n < 5; ++n) pbuf[15 + n][l] = FP.x[n];
+      }
+    } else {
+#pragma unroll
+      for (int n = 0; n < 15; ++n) FP.c[n] = pbuf[n][l];
+#pragma unroll
+      for (int n = 0; n < 5; ++n) FP.x[n] = pbuf[15 + n][l];
+      relative_momentum<TR, TM>(B, sb, sc, st, l, nd, un, FN);
+    }
+    if constexpr (FIELDS) {
+      add_fields(FP, -hc, FN, F);
+      recon_field<TR, SI, true>(P, F, C, &a);
+    }
+    {
+      const TR a0 = (TR)a;
+#pragma unroll
+      for (int n = 0; n < 15; ++n) S[n] = n < 3 ? C[n] : a0 * C[n];  // P0
+    }
+    if constexpr (FIELDS) {
+      add_fields(FP, hc, FN, F);
+      recon_field<TR, SI, true>(P, F, C, &a);
+    } else {
+      char_field<DIR, 3, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
+    }
+    {
+      const TR a3 = (TR)a;
+#pragma unroll
+      for (int n = 0; n < 15; ++n) {
+        const TR p0 = S[n];
+        const TR f = n < 3 ? (TR)1 : a3;
+        S[n] = f * C[n] + p0;
+        D[n] = f * C[n] - p0;
+      }
     }
   }
   // scheduling barriers keep the later fields apart (bounds register pressure;
@@ -268,7 +359,22 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
     TR C1[15];
     double a1;
     if (!have_c1) {
-      char_field<DIR, 1, SI, TR, TM>(P, pr, B, sb, sc, st, l, C1, a1);
+      if constexpr (FIELDS) {
+        Field FR;
+        Sten2 A;
+        read_stencil<4, TM>(B, sb, sc, st, l, 0, A);
+        make_field<TR>(A, FR);
+        if constexpr (PARKP) {
+#pragma unroll
+          for (int n = 0; n < 15; ++n) FP.c[n] = pbuf[n][l];
+#pragma unroll
+          for (int n = 0; n < 5; ++n) FP.x[n] = pbuf[15 + n][l];
+        }
+        add_fields(FR, -2.0, FP, FR);
+        recon_field<TR, SI, true>(P, FR, C1, &a1);
+      } else {
+        char_field<DIR, 1, SI, TR, TM>(P, pr, B, sb, sc, st, l, C1, a1);
+      }
       if constexpr (PARK) {  // parked in LDS for the other sweep
 #pragma unroll
         for (int n = 0; n < 15; ++n) c1buf[n][l] = C1[n];
@@ -290,8 +396,14 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
     }
   }
   if constexpr (!OVERLAP12) __builtin_amdgcn_sched_barrier(0);
-  char_field<DIR, 2, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
   {
+    if constexpr (FIELDS) {
+      Field FT;
+      relative_momentum<TR, TM>(B, sb, sc, st, l, td, ut, FT);
+      recon_field<TR, SI, true>(P, FT, C, &a);
+    } else {
+      char_field<DIR, 2, SI, TR, TM>(P, pr, B, sb, sc, st, l, C, a);
+    }
     const TR tut = (TR)ut, a2 = (TR)a, uta2 = (TR)(ut * a);
 #pragma unroll
     for (int n = 0; n < 15; ++n) {
@@ -321,6 +433,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
   constexpr bool IFACE = EQ == EQ_EULER && CHAR == 3;  // interface bases for edge values
   __shared__ RowBuf<NC, TM> B;
   __shared__ TR c1buf[16][64];  // entropy-field polynomial shared by the two sweeps
+  // p0 and cross values of the field P shared by the two sweeps
+  __shared__ double pbuf[CHAR == 1 && EQ == EQ_EULER && sizeof(TR) == 8 ? 20 : 1][64];
   // per-interface bases: the edge values of the low and the high edge of the
   // current direction, parked while the cell's own basis is reconstructed
   __shared__ TR ebuf[IFACE ? 2 * 3 * NC : 1][64];
@@ -483,8 +597,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
           return make_prim_roe<TR>(gm1, UL, UR);
         };
         // top edge, eta = +1/2, in the basis of y_{j+1/2}
-        char_sweep<1, SI, false, TR, TM>(P, roe_rows(sc, st), B, sb, sc, st, lane, Cc, c1buf,
-                                         false);
+        char_sweep<1, SI, false, false, TR, TM>(P, roe_rows(sc, st), B, sb, sc, st, lane, Cc, c1buf,
+                                         pbuf, false);
 #pragma unroll
         for (int G = 0; G < 3; ++G)
 #pragma unroll
@@ -497,8 +611,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
         __builtin_amdgcn_sched_barrier(0);
         if (j >= r0) {
           // bottom edge, eta = -1/2, in the basis of y_{j-1/2}
-          char_sweep<1, SI, false, TR, TM>(P, roe_rows(sb, sc), B, sb, sc, st, lane, Cc, c1buf,
-                                           false);
+          char_sweep<1, SI, false, false, TR, TM>(P, roe_rows(sb, sc), B, sb, sc, st, lane, Cc, c1buf,
+                                           pbuf, false);
 #pragma unroll
           for (int G = 0; G < 3; ++G)
 #pragma unroll
@@ -514,21 +628,23 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
 #pragma unroll
           for (int k = 0; k < 4; ++k) U5[k] = B.u[sc][k][lane + 1];
           pr = make_prim<TR>(gm1, U5);
-          char_sweep<1, SI, true, TR, TM>(P, pr, B, sb, sc, st, lane, Cc, c1buf, false);
+          char_sweep<1, SI, true, false, TR, TM>(P, pr, B, sb, sc, st, lane, Cc, c1buf, pbuf, false);
         }
       } else if constexpr (PROJ) {
         double U5[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) U5[k] = B.u[sc][k][lane + 1];
         pr = make_prim<TR>(gm1, U5);
-        char_sweep<SPLIT ? 1 : 0, SI, SPLIT, TR, TM, SPLIT && sizeof(TR) == 8>(
-            P, pr, B, sb, sc, st, lane, Cc, c1buf, false);
+        char_sweep<SPLIT ? 1 : 0, SI, SPLIT, SPLIT, TR, TM, SPLIT && sizeof(TR) == 8>(
+            P, pr, B, sb, sc, st, lane, Cc, c1buf, pbuf, false);
       } else {
 #pragma unroll
         for (int k = 0; k < NC; ++k) {
           Sten2 S;
+          Field F;
           read_stencil<NC, TM>(B, sb, sc, st, lane, k, S);
-          recon_scalar<TR, SI>(P, S, Cc[k]);
+          make_field<TR>(S, F);
+          recon_field<TR, SI>(P, F, Cc[k]);
         }
       }
       // y-edges at (xi_G, -+1/2), interior values for g (and f when the
@@ -654,8 +770,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
             return make_prim_roe<TR>(gm1, UL, UR);
           };
           // left edge, xi = -1/2, in the basis of x_{i-1/2}
-          char_sweep<0, SI, false, TR, TM>(P, roe_cols(0), B, sb, sc, st, lane, Cc, c1buf,
-                                           false);
+          char_sweep<0, SI, false, false, TR, TM>(P, roe_cols(0), B, sb, sc, st, lane, Cc, c1buf,
+                                           pbuf, false);
 #pragma unroll
           for (int H = 0; H < 3; ++H)
 #pragma unroll
@@ -667,8 +783,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
             }
           __builtin_amdgcn_sched_barrier(0);
           // right edge, xi = +1/2, in the basis of x_{i+1/2}
-          char_sweep<0, SI, false, TR, TM>(P, roe_cols(1), B, sb, sc, st, lane, Cc, c1buf,
-                                           false);
+          char_sweep<0, SI, false, false, TR, TM>(P, roe_cols(1), B, sb, sc, st, lane, Cc, c1buf,
+                                           pbuf, false);
 #pragma unroll
           for (int H = 0; H < 3; ++H)
 #pragma unroll
@@ -685,8 +801,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
           pr = make_prim<TR>(gm1, U5);
         }
         if constexpr (SPLIT)
-          char_sweep<0, SI, false, TR, TM, !IFACE && sizeof(TR) == 8>(P, pr, B, sb, sc, st, lane,
-                                                                      Cc, c1buf, true);
+          char_sweep<0, SI, false, !IFACE, TR, TM, !IFACE && sizeof(TR) == 8>(P, pr, B, sb, sc, st, lane,
+                                                                      Cc, c1buf, pbuf, true);
         double F1x[NC];
         TR F2x[NC], F3x[NC];
 #pragma unroll
