@@ -49,6 +49,8 @@ struct hwenou_handle {
   double *d_alpha = nullptr, *d_alpha_next = nullptr, *d_dt = nullptr, *d_t = nullptr;
   int *d_steps = nullptr, *d_done = nullptr, *d_status = nullptr, *d_all_done = nullptr;
   int* h_flags = nullptr;            // pinned [2]: all-done flags of the last two chunks
+  double* d_part = nullptr;          // partial maxima of the wave-speed reduction
+  int part_blocks = 1;
   RunParams* d_run = nullptr;        // parameters of the current hwenou_advance call
   RunParams* h_run = nullptr;        // pinned staging copy
   hipEvent_t ev_poll[2] = {nullptr, nullptr};
@@ -127,7 +129,7 @@ void free_handle(hwenou_handle* h) {
     if (p) (void)hipFree(p);
   };
   f(h->d_inst); f(h->d_alpha); f(h->d_alpha_next); f(h->d_dt); f(h->d_t);
-  f(h->d_steps); f(h->d_done); f(h->d_status); f(h->d_all_done); f(h->d_run);
+  f(h->d_steps); f(h->d_done); f(h->d_status); f(h->d_all_done); f(h->d_run); f(h->d_part);
   f(h->m_base); f(h->s1u); f(h->s2u); f(h->s1m); f(h->s2m);
   f(h->d_work); f(h->d_work_ptr);
   f(h->d_tiles); f(h->d_state); f(h->d_flag); f(h->d_acc);
@@ -411,6 +413,8 @@ AuxArgs aux_args(hwenou_handle* h, const double* u) {
   a.u = u;
   a.alpha = h->d_alpha;
   a.alpha_stride = 2;
+  a.part = h->d_part;
+  a.part_blocks = h->part_blocks;
   a.dt = h->d_dt;
   a.t = h->d_t;
   a.steps = h->d_steps;
@@ -560,6 +564,11 @@ int hwenou_create(const hwenou_desc* d, int n_inst, const hwenou_inst* inst, voi
   TRY(dalloc(&h->d_status, n_inst));
   TRY(dalloc(&h->d_all_done, 1));
   TRY(dalloc(&h->d_run, 1));
+  for (int k = 0; k < n_inst; ++k)
+    h->part_blocks = std::max(
+        h->part_blocks, speed_blocks((long long)inst[k].nx * (d->dim == 1 ? 1 : inst[k].ny),
+                                     kSpeedBlocks));
+  TRY(dalloc(&h->d_part, 2 * (size_t)h->part_blocks * n_inst));
   TRY(dalloc_bytes(&h->m_base, mom_bytes));
   TRY(dalloc(&h->s1u, u_count));
   TRY(dalloc(&h->s2u, u_count));
@@ -658,7 +667,7 @@ int hwenou_autotune(hwenou_handle* h, const double* ubar, const void* mom, int r
   HIPCHK(hipStreamWaitEvent(st, h->ev_in, 0));
   HIPCHK(hipMemsetAsync(h->d_dt, 0, h->n_inst * sizeof(double), st));
   AuxArgs a = aux_args(h, ubar);
-  hipError_t e = launch_max_wavespeed(a, true, st);
+  hipError_t e = launch_max_wavespeed(a, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   hipEvent_t t0, t1;
   HIPCHK(hipEventCreate(&t0));
@@ -713,7 +722,7 @@ int hwenou_max_wavespeed(hwenou_handle* h, const double* ubar, double* alpha_dev
     return HWENOU_EINVAL;
   AuxArgs a = aux_args(h, ubar);
   a.alpha = alpha_dev;
-  hipError_t e = launch_max_wavespeed(a, true, h->stream);
+  hipError_t e = launch_max_wavespeed(a, h->stream);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   return HWENOU_OK;
 }
@@ -795,7 +804,7 @@ int advance_whole_steps(hwenou_handle* h, double* ubar, void* mom, const RunPara
   a.alpha = r.acc[0];
   a.alpha_stride = kAlphaStride * h->step_slots;
   a.status = r.flag[0];
-  e = launch_max_wavespeed(a, false, st);
+  e = launch_max_wavespeed(a, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
 
   const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
@@ -889,7 +898,7 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
   HIPCHK(hipMemsetAsync(h->d_done, 0, h->n_inst * sizeof(int), st));
   HIPCHK(hipMemsetAsync(h->d_status, 0, h->n_inst * sizeof(int), st));
   AuxArgs a = aux_args(h, ubar);
-  hipError_t e = launch_max_wavespeed(a, true, st);
+  hipError_t e = launch_max_wavespeed(a, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
   // the first step's dt; later ones are set by the finish kernel of the step before
   e = launch_dt(a, st);

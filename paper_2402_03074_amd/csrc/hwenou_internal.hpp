@@ -163,6 +163,14 @@ hipError_t launch_step_1d(int eq, int char_mode, bool mixed, const void* args, i
 int occupancy_step_1d(int eq, int char_mode, bool mixed, int threads);
 
 // auxiliary kernels
+// Blocks of the wave-speed reduction of an instance of n cells, at most `most`.
+constexpr int kSpeedThreads = 1024;
+constexpr int kSpeedCells = 8 * kSpeedThreads;  // per block, up to 512 blocks per instance
+constexpr int kSpeedBlocks = 512;
+__device__ __host__ __forceinline__ int speed_blocks(long long n, int most) {
+  const long long b = (n + kSpeedCells - 1) / kSpeedCells;
+  return b < most ? (int)b : most;
+}
 struct AuxArgs {
   SchemeParams P;
   int eq, dim, n_inst;
@@ -171,6 +179,8 @@ struct AuxArgs {
   const double* u;       // [nc][plane]
   double* alpha;         // [n_inst][alpha_stride]: x and y wave speed first
   int alpha_stride;
+  double* part;          // [n_inst][part_blocks][2] partial maxima
+  int part_blocks;       // speed_blocks of the largest instance
   double* dt;            // [n_inst]
   double* t;             // [n_inst]
   int* steps;            // [n_inst]
@@ -181,8 +191,7 @@ struct AuxArgs {
   const RunParams* run;  // CFL number, final time, step limit
   int* all_done;         // 1 when every instance is done
 };
-// a.alpha must be zero on entry unless `zero` asks for it to be cleared first
-hipError_t launch_max_wavespeed(const AuxArgs& a, bool zero, hipStream_t s);
+hipError_t launch_max_wavespeed(const AuxArgs& a, hipStream_t s);
 hipError_t launch_dt(const AuxArgs& a, hipStream_t s);
 hipError_t launch_finish(const AuxArgs& a, hipStream_t s);
 

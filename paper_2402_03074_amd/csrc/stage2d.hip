@@ -261,7 +261,7 @@ __device__ __forceinline__ void char_field(const SchemeParams& P, const Prim& pr
 // from the first sweep to the second through LDS (PARKP).  Per cell and both
 // directions that is about 620 operations and 190 LDS reads of stencil values,
 // where projecting each of the seven field-sweeps and forming its p0 takes 930
-// and 270.  2048^2 grid: 2.20 -> 2.13 ms per Runge-Kutta step; 500 x 333 with
+// and 270.  2048^2 grid: 2.20 -> 2.11 ms per Runge-Kutta step; 500 x 333 with
 // per-interface bases: 320 -> 293 us.
 // The mixed form projects field by field (char_field): its FP32 results are
 // bound to the FP64 rounding in front of them (see p0_coeffs_2d).
@@ -336,6 +336,9 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
       for (int n = 0; n < 15; ++n) S[n] = n < 3 ? C[n] : a0 * C[n];  // P0
     }
     if constexpr (FIELDS) {
+      // fields 0 and 3 one after the other: 1% faster than overlapped, which
+      // took the registers of the stencil reads they used to share
+      __builtin_amdgcn_sched_barrier(0);
       add_fields(FP, hc, FN, F);
       recon_field<TR, SI, true>(P, F, C, &a);
     } else {
