@@ -40,9 +40,6 @@ HBM_PEAK_GBS = 8000.0
 # FP64 vector peak of MI355X: 256 CUs x 4 SIMDs x 16 lanes x 2 flops x 2.4 GHz;
 # non-packed FP32 runs at the same instruction rate
 VALU_PEAK_TFLOPS = 78.6
-# finish kernel of one step, which also sets the next dt (rocprofv3 kernel
-# trace: ~4 us)
-AUX_US_PER_STEP = 4.0
 # the counters also depend on the work lists the host library builds (which
 # wave reads which rows and columns) and on the compiler flags of each source
 # (the instruction scheduler), so those sources are hashed with the kernels
@@ -57,7 +54,9 @@ COUNTERS = {
     2: ("stage2d_kernel", "profiles/stage2d_euler_2048_counters.md", "euler2d-2048",
         KERNEL_SOURCES),
     1: ("stage1d_kernel", "profiles/stage1d_euler_batch512_counters.md", "euler1d-batch512",
-        ["paper_2402_03074_amd/csrc/stage1d.hip"] + COMMON_SOURCES),
+        ["paper_2402_03074_amd/csrc/stage1d.hip", "paper_2402_03074_amd/csrc/step1d.hip",
+         "paper_2402_03074_amd/csrc/tile1d.hpp",
+         "paper_2402_03074_amd/csrc/tile1d_terms.inc"] + COMMON_SOURCES),
 }
 COUNTERS_FILE = COUNTERS[2][1]
 DEFAULT_WORKLOAD = "euler2d-2048"
@@ -219,11 +218,9 @@ def run_case(H, torch, case, precision, steps, warmup, tune, char_decomp=True, l
     ev_ms = e0.elapsed_time(e1)
     assert sg == [steps] * len(case.insts), sg
 
-    # The timed region is graph replays of whole steps: per step three
-    # launches of the stage kernel and one finish kernel (a single block,
-    # ~4 us by the kernel trace), so the stage kernel's average launch
-    # duration implied by the timed region is (region / steps - aux) / 3.
-    stage_ms_region = (ev_ms / steps - AUX_US_PER_STEP * 1e-3) / 3.0
+    # The timed region is whole steps: three launches of the stage kernel each
+    # (in 1D one launch of the whole-step kernel, so a third of its time).
+    stage_ms_region = ev_ms / steps / 3.0
     # right after the timed region, while the clocks are up
     stage_ms = stage_launch_ms(H, torch, S, case, ug, mg, max(3, min(steps, 20)))
     status = H.hwenou_status(S.h)

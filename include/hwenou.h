@@ -165,9 +165,9 @@ int hwenou_stage(hwenou_handle* h, int s, const double* dt_dev, const double* al
  * CFL number (0.6 in Section 3) but not the formula; this is the usual one.
  * alpha and dt stay on the device.  In 1D a whole step is one launch on the
  * handle's stream (unless an instance has exactly one periodic side); in 2D,
- * and for such 1D handles, whole steps (the three stages and a finish kernel
- * that also sets the next dt) are replayed from a HIP graph, which is captured
- * on the first call and kept while the state pointers and the launch shape
+ * and for such 1D handles, a step is one launch per stage, and runs of eight
+ * steps are replayed from a HIP graph, which is captured on the first call of
+ * at least that many and kept while the state pointers and the launch shape
  * stay the same.  The host reads a completion flag after each chunk of steps
  * without waiting for the chunk in flight, and synchronises at the end.  An instance whose state leaves the physical
  * states (rho <= 0, p <= 0 or non-finite, flagged by any of its kernels)

@@ -1,10 +1,10 @@
 // Auxiliary kernels of the time loop: the maximum wave speed
 // alpha = max |f'(u)| over the cell averages (Section 2.1, used by the
-// Lax-Friedrichs flux and the CFL condition), the per-instance time step
-// dt = min(CFL dx / alpha, T - t) in 1D and CFL / (alpha_1/dx + alpha_2/dy)
-// in 2D, and the per-step bookkeeping of t, the step count and completion.
-// All per-instance state lives on the device so that whole steps can be
-// replayed from a captured graph without host synchronisation.
+// Lax-Friedrichs flux and the CFL condition), and the start, polls and end of
+// a run of steps.  The steps themselves form their time step
+// dt = min(CFL dx / alpha, T - t) in 1D and CFL / (alpha_1/dx + alpha_2/dy) in
+// 2D in the stage kernels (step_dt).  All per-instance state lives on the
+// device, so steps follow each other without host synchronisation.
 #include <algorithm>
 
 #include "hwenou_internal.hpp"
@@ -104,125 +104,7 @@ hipError_t launch_max_wavespeed(const AuxArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Time step of instance k for the step that starts at time t after `steps`
-// steps, from its wave speeds (ax, ay); marks the instance done when it has
-// reached t_final or max_steps, or when a kernel has flagged one of its
-// states as non-physical or non-finite (dt = 0 then: the instance stops at
-// the step that failed, and its t and step count say where).  The wave
-// speeds are reduced with fmax, which drops NaN arguments, so a NaN state is
-// caught by the flag, not by alpha.  The caller passes the values it has
-// loaded, so that each step's bookkeeping costs one round of loads.  Returns
-// whether the instance is done.
-__device__ bool set_step(const AuxArgs& A, int k, const InstDev& I, const RunParams& R, bool done,
-                         double t, int steps, int status, double ax, double ay) {
-  const bool finished = done || steps >= R.max_steps || t >= R.t_final * (1.0 - 1e-14);
-  if (finished || status) {
-    A.done[k] = 1;
-    A.dt[k] = 0.0;
-    return true;
-  }
-  if (A.dim == 1) ay = 0.0;
-  if (!isfinite(ax) || !isfinite(ay)) {  // infinite wave speed: stop and report it
-    A.done[k] = 1;
-    A.dt[k] = 0.0;
-    atomicOr(&A.status[k], 1);
-    return true;
-  }
-  double dt;
-  if (ax == 0.0 && ay == 0.0)
-    dt = R.t_final - t;  // zero wave speed: every flux vanishes, the CFL bound is infinite
-  else if (A.dim == 1)
-    dt = R.cfl * I.dx / ax;
-  else
-    dt = R.cfl / (ax / I.dx + ay / I.dy);
-  if (t + dt > R.t_final) dt = R.t_final - t;
-  A.dt[k] = dt;
-  return false;
-}
-
-// Before the first step: its time step, and the reset of the wave-speed
-// accumulators that the last stage of the step fills.
-__global__ __launch_bounds__(256) void dt_kernel(const AuxArgs A) {
-  for (int k = threadIdx.x; k < A.n_inst * A.alpha_slots; k += blockDim.x) {
-    A.alpha_next[kAlphaStride * k] = 0.0;
-    A.alpha_next[kAlphaStride * k + 1] = 0.0;
-  }
-  for (int k = threadIdx.x; k < A.n_inst; k += blockDim.x)
-    set_step(A, k, A.inst[k], *A.run, A.done[k] != 0, A.t[k], A.steps[k], A.status[k],
-             A.alpha[2 * k], A.alpha[2 * k + 1]);
-}
-
-// End of a step: advance t and the step count, take the new wave speed,
-// reset its accumulator, set the next step's time step, and count the
-// instances still running (read by the host every few steps).  Everything
-// an instance needs is loaded up front, in one round of loads.
-__global__ __launch_bounds__(256) void finish_kernel(const AuxArgs A) {
-  __shared__ int running;
-  if (threadIdx.x == 0) running = 0;
-  __syncthreads();
-  int mine = 0;
-  const RunParams R = *A.run;
-  for (int k = threadIdx.x; k < A.n_inst; k += blockDim.x) {
-    double* acc = A.alpha_next + alpha_slot(k, 0, A.alpha_slots);
-    const bool done = A.done[k] != 0;
-    double t = A.t[k];
-    const double dt = A.dt[k];
-    int steps = A.steps[k];
-    const int status = A.status[k];
-    const InstDev I = A.inst[k];
-    // every slot line of the allocation is loaded at once (in bounds: the
-    // array holds kAlphaSlots lines per instance), and those beyond this
-    // instance's slots count as zero (the wave speeds are non-negative)
-    double sx[kAlphaSlots], sy[kAlphaSlots];
-#pragma unroll
-    for (int s = 0; s < kAlphaSlots; ++s) {
-      sx[s] = acc[kAlphaStride * s];
-      sy[s] = acc[kAlphaStride * s + 1];
-    }
-    double ax, ay;
-    if (!done) {
-      t += dt;
-      steps += 1;
-      ax = sx[0];
-      ay = sy[0];
-#pragma unroll
-      for (int s = 1; s < kAlphaSlots; ++s) {
-        const bool own = s < A.alpha_slots;
-        ax = fmax(ax, own ? sx[s] : 0.0);
-        ay = fmax(ay, own ? sy[s] : 0.0);
-      }
-      A.t[k] = t;
-      A.steps[k] = steps;
-      A.alpha[2 * k] = ax;
-      A.alpha[2 * k + 1] = ay;
-    } else {
-      ax = ay = 0.0;  // unused: a done instance stays done
-    }
-#pragma unroll
-    for (int s = 0; s < kAlphaSlots; ++s) {
-      if (s < A.alpha_slots) {
-        acc[kAlphaStride * s] = 0.0;
-        acc[kAlphaStride * s + 1] = 0.0;
-      }
-    }
-    if (!set_step(A, k, I, R, done, t, steps, status, ax, ay)) mine = 1;
-  }
-  if (mine) atomicOr(&running, 1);
-  __syncthreads();
-  if (threadIdx.x == 0) A.all_done[0] = running ? 0 : 1;
-}
-
-hipError_t launch_dt(const AuxArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(dt_kernel, dim3(1), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_finish(const AuxArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(finish_kernel, dim3(1), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-// Start of a run of whole 1D steps: the call's parameters, zero time and step
+// Start of a run: the call's parameters, zero time and step
 // count, no flags, and zero wave-speed accumulators.
 __global__ __launch_bounds__(256) void run_begin_kernel(const RunArgs A) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x, nt = gridDim.x * blockDim.x;
@@ -238,6 +120,23 @@ __global__ __launch_bounds__(256) void run_begin_kernel(const RunArgs A) {
       A.acc[b][kAlphaStride * k] = 0.0;
       A.acc[b][kAlphaStride * k + 1] = 0.0;
     }
+}
+
+__global__ __launch_bounds__(256) void step_control_kernel(const ControlArgs A) {
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < A.n_inst; k += gridDim.x * blockDim.x) {
+    const StepDt d = step_dt<1>(A.ctl, k, A.inst[k]);
+    write_step(A.ctl, k, d);
+    A.dt[k] = d.dt;
+    A.alpha[2 * k] = d.ax;
+    A.alpha[2 * k + 1] = 0.0;
+    A.done[k] = d.done;
+  }
+}
+
+hipError_t launch_step_control(const ControlArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(step_control_kernel, dim3(std::min(256, (a.n_inst + 255) / 256)), dim3(256), 0,
+                     s, a);
+  return hipGetLastError();
 }
 
 // Between chunks of steps: whether any instance would take another step.
@@ -258,11 +157,25 @@ __global__ __launch_bounds__(256) void run_poll_kernel(const RunArgs A) {
   if (threadIdx.x == 0) *A.running_host = running;
 }
 
-// End of a run: the state of an instance that stopped after an odd number of
-// steps is in the scratch buffers and goes back to the caller's arrays; time,
-// step count and status go to the pinned host arrays.  One wave per tile.
-template <class TM>
+// Time, step count and status of an instance, into the pinned host arrays.
+__device__ __forceinline__ void report(const RunArgs& A, int inst, const StepState& s) {
+  const int f = A.flag[0][inst] | A.flag[1][inst];
+  A.status[inst] = f;
+  A.t_host[inst] = s.t;
+  A.steps_host[inst] = s.steps;
+  A.status_host[inst] = f;
+}
+
 __global__ __launch_bounds__(256) void run_end_kernel(const RunArgs A) {
+  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < A.n_inst; k += gridDim.x * blockDim.x)
+    report(A, k, A.st[A.last][k]);
+}
+
+// End of a run of whole 1D steps: the state of an instance that stopped after
+// an odd number of steps is in the scratch buffers and goes back to the
+// caller's arrays.  One wave per tile.
+template <class TM>
+__global__ __launch_bounds__(256) void run_end_tiles_kernel(const RunArgs A) {
   const int lane = threadIdx.x & 63, per = blockDim.x >> 6;
   const TM* m_odd = static_cast<const TM*>(A.m_odd);
   TM* m = static_cast<TM*>(A.m);
@@ -278,13 +191,7 @@ __global__ __launch_bounds__(256) void run_end_kernel(const RunArgs A) {
         for (int k = 0; k < A.mom_planes; ++k) m[k * A.plane + o] = m_odd[k * A.plane + o];
       }
     }
-    if (wk.start == 0 && lane == 0) {
-      const int f = A.flag[0][wk.inst] | A.flag[1][wk.inst];
-      A.status[wk.inst] = f;
-      A.t_host[wk.inst] = s.t;
-      A.steps_host[wk.inst] = s.steps;
-      A.status_host[wk.inst] = f;
-    }
+    if (wk.start == 0 && lane == 0) report(A, wk.inst, s);
   }
 }
 
@@ -301,10 +208,13 @@ hipError_t launch_run_poll(const RunArgs& a, hipStream_t s) {
 
 hipError_t launch_run_end(const RunArgs& a, hipStream_t s) {
   const int blocks = std::min(2048, (a.n_tiles + 3) / 4);
-  if (a.mom_elem == 4)
-    hipLaunchKernelGGL(run_end_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
+  if (a.tiles == nullptr)
+    hipLaunchKernelGGL(run_end_kernel, dim3(std::min(256, (a.n_inst + 255) / 256)), dim3(256), 0,
+                       s, a);
+  else if (a.mom_elem == 4)
+    hipLaunchKernelGGL(run_end_tiles_kernel<float>, dim3(blocks), dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(run_end_kernel<double>, dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(run_end_tiles_kernel<double>, dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -7,7 +7,6 @@
 #include <cstdio>
 #include <cstring>
 #include <string>
-#include <type_traits>
 #include <vector>
 
 #include "../../include/hwenou.h"
@@ -41,25 +40,35 @@ struct hwenou_handle {
   long long plane = 0;
   size_t mom_elem = 8;
   hipStream_t stream = nullptr;      // caller's stream
-  hipStream_t own = nullptr;         // capture stream of hwenou_advance
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
+  hipStream_t own = nullptr;         // capture stream, and the autotuner's
+  hipEvent_t ev_in = nullptr;
+  hipEvent_t ev_poll[2] = {nullptr, nullptr};
   std::vector<hwenou_inst> inst;
+  // per-instance device records and state, in one allocation
+  void* d_arena = nullptr;
   InstDev* d_inst = nullptr;
-  // per-instance device state
-  double *d_alpha = nullptr, *d_alpha_next = nullptr, *d_dt = nullptr, *d_t = nullptr;
-  int *d_steps = nullptr, *d_done = nullptr, *d_status = nullptr, *d_all_done = nullptr;
-  int* h_flags = nullptr;            // pinned [2]: all-done flags of the last two chunks
+  TileItem* d_tiles = nullptr;       // whole-step tiles (1D)
+  int* d_status = nullptr;
+  double *d_alpha = nullptr, *d_dt = nullptr;  // the autotuner's and the one-stage 1D steps'
+  int* d_done = nullptr;
+  RunParams* d_run = nullptr;        // parameters of the current hwenou_advance call
+  StepState* d_state = nullptr;      // [2][n_inst]
+  int* d_flag = nullptr;             // [2][n_inst]
   double* d_part = nullptr;          // partial maxima of the wave-speed reduction
   int part_blocks = 1;
-  RunParams* d_run = nullptr;        // parameters of the current hwenou_advance call
-  RunParams* h_run = nullptr;        // pinned staging copy
-  hipEvent_t ev_poll[2] = {nullptr, nullptr};
-  // the step graphs of hwenou_advance (one step, and kMultiSteps steps in a
-  // row), kept while the state pointers and the work lists stay the same
-  hipGraph_t graph[2] = {nullptr, nullptr};
-  hipGraphExec_t exec[2] = {nullptr, nullptr};
+  double* d_acc = nullptr;           // [4][n_inst][slots][kAlphaStride], with the work lists
+  size_t acc_lines = 0;              // n_inst * slots it has room for
+  // pinned host results of a run
+  double* h_t = nullptr;             // [n_inst]
+  int *h_steps = nullptr, *h_status = nullptr;  // [n_inst]
+  int* h_running = nullptr;          // [2]: whether any instance runs on, last two chunks
+  // the graph of kGraphSteps steps of hwenou_advance (one stage per launch),
+  // kept while the state pointers and the work lists stay the same
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
   const void *g_ubar = nullptr, *g_mom = nullptr;
-  // scratch of the time loop and the stage base
+  // scratch of the time loop and the stage base, in one allocation
+  void* d_scratch = nullptr;
   void* m_base = nullptr;            // v^_n (w^_n) [dim][nc][plane]
   double *s1u = nullptr, *s2u = nullptr;
   void *s1m = nullptr, *s2m = nullptr;
@@ -67,19 +76,13 @@ struct hwenou_handle {
   // whole steps in one launch (1D; step1d.hip): usable when every instance has
   // two periodic sides or none
   bool whole_steps = false;
-  TileItem* d_tiles = nullptr;
-  int n_tiles = 0, step_waves = 0, step_slots = 1;
-  StepState* d_state = nullptr;      // [2][n_inst]
-  int* d_flag = nullptr;             // [2][n_inst]
-  double* d_acc = nullptr;           // [4][n_inst][kAlphaSlots][kAlphaStride]
-  double* h_t = nullptr;             // pinned results of a run, [n_inst] each
-  int *h_steps = nullptr, *h_status = nullptr;
+  int n_tiles = 0, step_waves = 0;
   // work lists
   int waves_per_cu = 0, rows_per_item = 0;
   int n_cu = 256;
   int n_xcd = 8;  // chiplets, each with its own L2
-  int alpha_slots = 1;  // wave-speed accumulators per instance
-  WorkItem* d_work = nullptr;
+  int slots = 1;  // wave-speed accumulators per instance
+  WorkItem* d_work = nullptr;        // with d_work_ptr behind it
   int* d_work_ptr = nullptr;
   int n_waves = 0;
   bool work_dirty = true;
@@ -87,17 +90,7 @@ struct hwenou_handle {
 
 namespace {
 
-template <class T>
-int dalloc(T** p, size_t count) {
-  *p = nullptr;
-  if (count == 0) count = 1;
-  hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
-  if (e == hipErrorOutOfMemory) return HWENOU_ENOMEM;
-  if (e != hipSuccess) return hip_fail(e, "hipMalloc");
-  return HWENOU_OK;
-}
-
-int dalloc_bytes(void** p, size_t bytes) {
+int dalloc(void** p, size_t bytes) {
   *p = nullptr;
   hipError_t e = hipMalloc(p, bytes ? bytes : 1);
   if (e == hipErrorOutOfMemory) return HWENOU_ENOMEM;
@@ -105,41 +98,31 @@ int dalloc_bytes(void** p, size_t bytes) {
   return HWENOU_OK;
 }
 
+size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
+
 constexpr int kStepThreads = 256;  // block of the whole-step 1D kernel
 
-// Steps per replay of the multi-step graph: the gap between two graph
-// launches (~5-10 us) then falls on every kMultiSteps-th step only, which
-// matters for grids whose steps take tens of microseconds.
-constexpr int kMultiSteps = 8;
+// Steps per graph replay where a step is three launches; the rest of a call's
+// steps are launched one by one.  A multiple of four, the number of
+// accumulator buffers that the steps rotate through.
+constexpr int kGraphSteps = 8;
 
 void drop_graph(hwenou_handle* h) {
-  for (int g = 0; g < 2; ++g) {
-    if (h->exec[g]) (void)hipGraphExecDestroy(h->exec[g]);
-    if (h->graph[g]) (void)hipGraphDestroy(h->graph[g]);
-    h->exec[g] = nullptr;
-    h->graph[g] = nullptr;
-  }
+  if (h->exec) (void)hipGraphExecDestroy(h->exec);
+  if (h->graph) (void)hipGraphDestroy(h->graph);
+  h->exec = nullptr;
+  h->graph = nullptr;
   h->g_ubar = h->g_mom = nullptr;
 }
 
 void free_handle(hwenou_handle* h) {
   if (!h) return;
   drop_graph(h);
-  auto f = [](void* p) {
+  for (void* p : {h->d_arena, h->d_scratch, (void*)h->d_work, (void*)h->d_acc})
     if (p) (void)hipFree(p);
-  };
-  f(h->d_inst); f(h->d_alpha); f(h->d_alpha_next); f(h->d_dt); f(h->d_t);
-  f(h->d_steps); f(h->d_done); f(h->d_status); f(h->d_all_done); f(h->d_run); f(h->d_part);
-  f(h->m_base); f(h->s1u); f(h->s2u); f(h->s1m); f(h->s2m);
-  f(h->d_work); f(h->d_work_ptr);
-  f(h->d_tiles); f(h->d_state); f(h->d_flag); f(h->d_acc);
   if (h->h_t) (void)hipHostFree(h->h_t);
-  if (h->h_flags) (void)hipHostFree(h->h_flags);
-  if (h->h_run) (void)hipHostFree(h->h_run);
-  for (hipEvent_t e : h->ev_poll)
+  for (hipEvent_t e : {h->ev_poll[0], h->ev_poll[1], h->ev_in})
     if (e) (void)hipEventDestroy(e);
-  if (h->ev_in) (void)hipEventDestroy(h->ev_in);
-  if (h->ev_out) (void)hipEventDestroy(h->ev_out);
   if (h->own) (void)hipStreamDestroy(h->own);
   delete h;
 }
@@ -276,8 +259,22 @@ int build_work(hwenou_handle* h) {
     xcd_order(items, ptr, h->n_xcd);
   }
   h->n_waves = (int)ptr.size() - 1;
-  {
-    // waves per instance, for the number of wave-speed accumulators
+  // waves on the busiest instance, for the number of wave-speed accumulators:
+  // one per 64 of them, a power of two from 1 to kAlphaSlots
+  int busiest = 0;
+  if (h->whole_steps) {
+    int w = h->waves_per_cu;
+    if (w <= 0) {
+      const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
+      w = kStepThreads / 64 * occupancy_step_1d(h->desc.eq, chr, h->mixed, kStepThreads);
+      if (w <= 0) w = 4;
+    }
+    h->step_waves = (int)std::min<long long>(h->n_tiles, (long long)h->n_cu * w);
+    for (const hwenou_inst& I : h->inst) {
+      const long long nt = (I.nx + kStepWidth - 1) / kStepWidth;
+      busiest = std::max(busiest, (int)(nt * h->step_waves / h->n_tiles) + 1);
+    }
+  } else {
     std::vector<int> waves(h->n_inst, 0), last(h->n_inst, -1);
     for (int w = 0; w < h->n_waves; ++w)
       for (int i = ptr[w]; i < ptr[w + 1]; ++i) {
@@ -287,40 +284,35 @@ int build_work(hwenou_handle* h) {
           ++waves[k];
         }
       }
-    const int busiest = waves.empty() ? 0 : *std::max_element(waves.begin(), waves.end());
-    int slots = 1;
-    while (slots < kAlphaSlots && 64 * slots < busiest) slots *= 2;
-    h->alpha_slots = slots;
+    busiest = waves.empty() ? 0 : *std::max_element(waves.begin(), waves.end());
+  }
+  h->slots = 1;
+  while (h->slots < kAlphaSlots && 64 * h->slots < busiest) h->slots *= 2;
+  if (h->acc_lines < (size_t)h->n_inst * h->slots) {
+    if (h->d_acc) (void)hipFree(h->d_acc);
+    h->d_acc = nullptr;
+    h->acc_lines = (size_t)h->n_inst * h->slots;
+    void* q = nullptr;
+    const int rc = dalloc(&q, 4 * h->acc_lines * kAlphaStride * sizeof(double));
+    if (rc) {
+      h->acc_lines = 0;
+      return rc;
+    }
+    h->d_acc = static_cast<double*>(q);
   }
   if (h->d_work) (void)hipFree(h->d_work);
-  if (h->d_work_ptr) (void)hipFree(h->d_work_ptr);
   h->d_work = nullptr;
   h->d_work_ptr = nullptr;
-  int rc = dalloc(&h->d_work, items.size());
+  const size_t item_bytes = items.size() * sizeof(WorkItem), ptr_bytes = ptr.size() * sizeof(int);
+  void* q = nullptr;
+  const int rc = dalloc(&q, item_bytes + ptr_bytes);
   if (rc) return rc;
-  rc = dalloc(&h->d_work_ptr, ptr.size());
-  if (rc) return rc;
-  HIPCHK(hipMemcpy(h->d_work, items.data(), items.size() * sizeof(WorkItem),
-                   hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(h->d_work_ptr, ptr.data(), ptr.size() * sizeof(int), hipMemcpyHostToDevice));
-  if (h->whole_steps) {
-    // waves of the whole-step launch, and its accumulators by the same rule
-    int w = h->waves_per_cu;
-    if (w <= 0) {
-      const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
-      w = kStepThreads / 64 * occupancy_step_1d(h->desc.eq, chr, h->mixed, kStepThreads);
-      if (w <= 0) w = 4;
-    }
-    h->step_waves = (int)std::min<long long>(h->n_tiles, (long long)h->n_cu * w);
-    int most = 0;
-    for (int k = 0; k < h->n_inst; ++k) {
-      const long long nt = (h->inst[k].nx + kStepWidth - 1) / kStepWidth;
-      most = std::max(most, (int)(nt * h->step_waves / h->n_tiles) + 1);
-    }
-    int slots = 1;
-    while (slots < kAlphaSlots && 64 * slots < most) slots *= 2;
-    h->step_slots = slots;
-  }
+  h->d_work = static_cast<WorkItem*>(q);
+  h->d_work_ptr = reinterpret_cast<int*>(static_cast<char*>(q) + item_bytes);
+  std::vector<char> lists(item_bytes + ptr_bytes);
+  std::memcpy(lists.data(), items.data(), item_bytes);
+  std::memcpy(lists.data() + item_bytes, ptr.data(), ptr_bytes);
+  HIPCHK(hipMemcpy(q, lists.data(), lists.size(), hipMemcpyHostToDevice));
   h->work_dirty = false;
   return HWENOU_OK;
 }
@@ -344,14 +336,11 @@ namespace {
 
 bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// Wave-speed accumulators per instance (set with the work lists): one per
-// 64 waves that work on the busiest instance, a power of two from 1 to
-// kAlphaSlots.
-int alpha_slots(const hwenou_handle* h) { return h->alpha_slots; }
-
-int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha, const int* done,
-                 const double* u_in, const void* m_in, double* u_out, void* m_out,
-                 double* alpha_next, hipStream_t st) {
+// One stage launch: with the caller's dt and alpha (ctl.run == nullptr; flags
+// go to d_status), or as part of a run.
+int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
+                 const StepControl& ctl, const double* u_in, const void* m_in, double* u_out,
+                 void* m_out, hipStream_t st) {
   if (h->work_dirty) {
     int rc = build_work(h);
     if (rc) return rc;
@@ -363,18 +352,17 @@ int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
   auto fill = [&](auto& A, auto* mi, auto* mo, auto* mb) {
     A.P = P;
     A.inst = h->d_inst;
+    A.ctl = ctl;
     A.dt = dt;
     A.alpha = alpha;
-    A.done = done;
+    A.done = ctl.run && h->dim == 1 ? h->d_done : nullptr;
     A.u_in = u_in;
     A.m_in = mi;
     A.u_base = h->u_base;
     A.m_base = mb;
     A.u_out = u_out;
     A.m_out = mo;
-    A.alpha_next = alpha_next;
-    A.alpha_slots = alpha_slots(h);
-    A.status = h->d_status;
+    A.status = ctl.run ? ctl.flag_out : h->d_status;
     A.plane = h->plane;
     A.work = h->d_work;
     A.work_ptr = h->d_work_ptr;
@@ -382,7 +370,7 @@ int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
     A.stage = s;
   };
   if (h->mixed) {
-    StageArgs<float> A;
+    StageArgs<float> A{};
     fill(A, static_cast<const float*>(m_in), static_cast<float*>(m_out),
          static_cast<float*>(h->m_base));
     if (h->dim == 1)
@@ -390,7 +378,7 @@ int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
     else
       e = launch_stage_2d(h->desc.eq, chr, true, si, &A, h->n_waves, 64, st);
   } else {
-    StageArgs<double> A;
+    StageArgs<double> A{};
     fill(A, static_cast<const double*>(m_in), static_cast<double*>(m_out),
          static_cast<double*>(h->m_base));
     if (h->dim == 1)
@@ -403,7 +391,7 @@ int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
 }
 
 AuxArgs aux_args(hwenou_handle* h, const double* u) {
-  AuxArgs a;
+  AuxArgs a{};
   a.P = scheme_params(h->desc);
   a.eq = h->desc.eq;
   a.dim = h->dim;
@@ -415,15 +403,7 @@ AuxArgs aux_args(hwenou_handle* h, const double* u) {
   a.alpha_stride = 2;
   a.part = h->d_part;
   a.part_blocks = h->part_blocks;
-  a.dt = h->d_dt;
-  a.t = h->d_t;
-  a.steps = h->d_steps;
-  a.done = h->d_done;
   a.status = h->d_status;
-  a.alpha_next = h->d_alpha_next;
-  a.alpha_slots = alpha_slots(h);
-  a.run = h->d_run;
-  a.all_done = h->d_all_done;
   return a;
 }
 
@@ -542,65 +522,76 @@ int hwenou_create(const hwenou_desc* d, int n_inst, const hwenou_inst* inst, voi
       h->n_xcd = nx;
   }
 
-  std::vector<InstDev> di(n_inst);
-  for (int k = 0; k < n_inst; ++k) di[k] = inst_dev(d, inst[k]);
-  const size_t mom_bytes = (size_t)h->dim * h->nc * plane * h->mom_elem;
-  const size_t u_count = (size_t)h->nc * plane;
-#define TRY(x)            \
-  do {                    \
-    rc = (x);             \
-    if (rc) {             \
-      free_handle(h);     \
-      return rc;          \
-    }                     \
-  } while (0)
-  TRY(dalloc(&h->d_inst, n_inst));
-  TRY(dalloc(&h->d_alpha, 2 * n_inst));
-  TRY(dalloc(&h->d_alpha_next, (size_t)kAlphaStride * kAlphaSlots * n_inst));
-  TRY(dalloc(&h->d_dt, n_inst));
-  TRY(dalloc(&h->d_t, n_inst));
-  TRY(dalloc(&h->d_steps, n_inst));
-  TRY(dalloc(&h->d_done, n_inst));
-  TRY(dalloc(&h->d_status, n_inst));
-  TRY(dalloc(&h->d_all_done, 1));
-  TRY(dalloc(&h->d_run, 1));
+  // records: instances, whole-step tiles, status (uploaded); the rest is written
+  // by the calls that use it
+  std::vector<TileItem> tiles;
+  if (d->dim == 1) {
+    h->whole_steps = true;
+    for (int k = 0; k < n_inst; ++k)
+      if ((inst[k].bc[0] == HWENOU_BC_PERIODIC) != (inst[k].bc[1] == HWENOU_BC_PERIODIC))
+        h->whole_steps = false;
+  }
+  if (h->whole_steps)
+    for (int k = 0; k < n_inst; ++k)
+      for (int s = 0; s < inst[k].nx; s += kStepWidth) tiles.push_back({k, s});
+  h->n_tiles = (int)tiles.size();
   for (int k = 0; k < n_inst; ++k)
     h->part_blocks = std::max(
         h->part_blocks, speed_blocks((long long)inst[k].nx * (d->dim == 1 ? 1 : inst[k].ny),
                                      kSpeedBlocks));
-  TRY(dalloc(&h->d_part, 2 * (size_t)h->part_blocks * n_inst));
-  TRY(dalloc_bytes(&h->m_base, mom_bytes));
-  TRY(dalloc(&h->s1u, u_count));
-  TRY(dalloc(&h->s2u, u_count));
-  TRY(dalloc_bytes(&h->s1m, mom_bytes));
-  TRY(dalloc_bytes(&h->s2m, mom_bytes));
-  if (d->dim == 1) {
-    std::vector<TileItem> tiles;
-    h->whole_steps = true;
-    for (int k = 0; k < n_inst; ++k) {
-      if ((inst[k].bc[0] == HWENOU_BC_PERIODIC) != (inst[k].bc[1] == HWENOU_BC_PERIODIC))
-        h->whole_steps = false;
-      for (int s = 0; s < inst[k].nx; s += kStepWidth) tiles.push_back({k, s});
-    }
-    h->n_tiles = (int)tiles.size();
-    if (h->whole_steps) {
-      TRY(dalloc(&h->d_tiles, tiles.size()));
-      TRY(dalloc(&h->d_state, 2 * (size_t)n_inst));
-      TRY(dalloc(&h->d_flag, 2 * (size_t)n_inst));
-      TRY(dalloc(&h->d_acc, 4 * (size_t)kAlphaStride * kAlphaSlots * n_inst));
-      hipError_t et = hipMemcpy(h->d_tiles, tiles.data(), tiles.size() * sizeof(TileItem),
-                                hipMemcpyHostToDevice);
-      if (et == hipSuccess)
-        et = hipHostMalloc(reinterpret_cast<void**>(&h->h_t), n_inst * (sizeof(double) + 2 * sizeof(int)));
-      if (et != hipSuccess) {
-        free_handle(h);
-        return hip_fail(et, "hipMemcpy / hipHostMalloc");
-      }
-      h->h_steps = reinterpret_cast<int*>(h->h_t + n_inst);
-      h->h_status = h->h_steps + n_inst;
-    }
+  const size_t n = n_inst;
+  size_t at = 0;
+  auto place = [&at](size_t bytes) {
+    const size_t o = at;
+    at += align256(bytes);
+    return o;
+  };
+  const size_t o_inst = place(n * sizeof(InstDev)), o_tiles = place(tiles.size() * sizeof(TileItem)),
+               o_status = place(n * sizeof(int));
+  std::vector<char> records(at, 0);
+  for (int k = 0; k < n_inst; ++k) {
+    const InstDev I = inst_dev(d, inst[k]);
+    std::memcpy(records.data() + o_inst + k * sizeof(InstDev), &I, sizeof I);
   }
-#undef TRY
+  if (!tiles.empty())
+    std::memcpy(records.data() + o_tiles, tiles.data(), tiles.size() * sizeof(TileItem));
+  const size_t o_alpha = place(2 * n * sizeof(double)), o_dt = place(n * sizeof(double)),
+               o_done = place(n * sizeof(int)),
+               o_run = place(sizeof(RunParams)), o_state = place(2 * n * sizeof(StepState)),
+               o_flag = place(2 * n * sizeof(int)),
+               o_part = place(2 * n * h->part_blocks * sizeof(double));
+  const size_t arena_bytes = at;
+  // scratch: the stored modified moments and the stage buffers (whole steps
+  // alternate between the caller's arrays and one stage buffer)
+  const size_t mom_bytes = (size_t)h->dim * h->nc * plane * h->mom_elem;
+  const size_t u_bytes = (size_t)h->nc * plane * sizeof(double);
+  at = 0;
+  const size_t o_base = place(mom_bytes), o_s1u = place(u_bytes), o_s1m = place(mom_bytes);
+  const size_t o_s2u = h->whole_steps ? 0 : place(u_bytes);
+  const size_t o_s2m = h->whole_steps ? 0 : place(mom_bytes);
+  if ((rc = dalloc(&h->d_arena, arena_bytes)) || (rc = dalloc(&h->d_scratch, at))) {
+    free_handle(h);
+    return rc;
+  }
+  char* arena = static_cast<char*>(h->d_arena);
+  h->d_inst = reinterpret_cast<InstDev*>(arena + o_inst);
+  h->d_tiles = reinterpret_cast<TileItem*>(arena + o_tiles);
+  h->d_status = reinterpret_cast<int*>(arena + o_status);
+  h->d_alpha = reinterpret_cast<double*>(arena + o_alpha);
+  h->d_dt = reinterpret_cast<double*>(arena + o_dt);
+  h->d_done = reinterpret_cast<int*>(arena + o_done);
+  h->d_run = reinterpret_cast<RunParams*>(arena + o_run);
+  h->d_state = reinterpret_cast<StepState*>(arena + o_state);
+  h->d_flag = reinterpret_cast<int*>(arena + o_flag);
+  h->d_part = reinterpret_cast<double*>(arena + o_part);
+  char* scratch = static_cast<char*>(h->d_scratch);
+  h->m_base = scratch + o_base;
+  h->s1u = reinterpret_cast<double*>(scratch + o_s1u);
+  h->s1m = scratch + o_s1m;
+  if (!h->whole_steps) {
+    h->s2u = reinterpret_cast<double*>(scratch + o_s2u);
+    h->s2m = scratch + o_s2m;
+  }
   auto chk = [&](hipError_t e2, const char* what) {
     if (e2 != hipSuccess) {
       rc = hip_fail(e2, what);
@@ -608,19 +599,20 @@ int hwenou_create(const hwenou_desc* d, int n_inst, const hwenou_inst* inst, voi
     }
     return true;
   };
-  if (!chk(hipHostMalloc(reinterpret_cast<void**>(&h->h_flags), 2 * sizeof(int)), "hipHostMalloc") ||
-      !chk(hipHostMalloc(reinterpret_cast<void**>(&h->h_run), sizeof(RunParams)), "hipHostMalloc") ||
-      !chk(hipMemcpy(h->d_inst, di.data(), n_inst * sizeof(InstDev), hipMemcpyHostToDevice),
-           "hipMemcpy") ||
-      !chk(hipMemset(h->d_status, 0, n_inst * sizeof(int)), "hipMemset") ||
+  if (!chk(hipHostMalloc(reinterpret_cast<void**>(&h->h_t),
+                         n * (sizeof(double) + 2 * sizeof(int)) + 2 * sizeof(int)),
+           "hipHostMalloc") ||
+      !chk(hipMemcpy(arena, records.data(), records.size(), hipMemcpyHostToDevice), "hipMemcpy") ||
       !chk(hipEventCreateWithFlags(&h->ev_poll[0], hipEventDisableTiming), "hipEventCreate") ||
       !chk(hipEventCreateWithFlags(&h->ev_poll[1], hipEventDisableTiming), "hipEventCreate") ||
-      !chk(hipStreamCreateWithFlags(&h->own, hipStreamNonBlocking), "hipStreamCreate") ||
       !chk(hipEventCreateWithFlags(&h->ev_in, hipEventDisableTiming), "hipEventCreate") ||
-      !chk(hipEventCreateWithFlags(&h->ev_out, hipEventDisableTiming), "hipEventCreate")) {
+      !chk(hipStreamCreateWithFlags(&h->own, hipStreamNonBlocking), "hipStreamCreate")) {
     free_handle(h);
     return rc;
   }
+  h->h_steps = reinterpret_cast<int*>(h->h_t + n);
+  h->h_status = h->h_steps + n;
+  h->h_running = h->h_status + n;
   rc = build_work(h);
   if (rc) {
     free_handle(h);
@@ -685,8 +677,8 @@ int hwenou_autotune(hwenou_handle* h, const double* ubar, const void* mom, int r
       std::vector<float> ts;
       for (int k = 0; k <= reps && !rc; ++k) {  // first launch warms up
         if (hipEventRecord(t0, st) != hipSuccess) rc = HWENOU_EHIP;
-        if (!rc) rc = launch_stage(h, 0, h->d_dt, h->d_alpha, nullptr, ubar, mom, h->s1u, h->s1m,
-                                   nullptr, st);
+        if (!rc)
+          rc = launch_stage(h, 0, h->d_dt, h->d_alpha, {}, ubar, mom, h->s1u, h->s1m, st);
         if (!rc && hipEventRecord(t1, st) != hipSuccess) rc = HWENOU_EHIP;
         if (!rc && hipEventSynchronize(t1) != hipSuccess) rc = HWENOU_EHIP;
         float ms = 0.f;
@@ -738,8 +730,7 @@ int hwenou_stage(hwenou_handle* h, int s, const double* dt_dev, const double* al
   if (ubar_in == ubar_out || mom_in == mom_out) return HWENOU_EINVAL;
   if (s == 0) h->u_base = ubar_in;
   if (s > 0 && h->u_base == nullptr) return HWENOU_EINVAL;
-  return launch_stage(h, s, dt_dev, alpha_dev, nullptr, ubar_in, mom_in, ubar_out, mom_out,
-                      nullptr, h->stream);
+  return launch_stage(h, s, dt_dev, alpha_dev, {}, ubar_in, mom_in, ubar_out, mom_out, h->stream);
 }
 
 int hwenou_inst_status(hwenou_handle* h, int* flags) {
@@ -763,109 +754,81 @@ int hwenou_status(hwenou_handle* h) { return hwenou_inst_status(h, nullptr); }
 
 namespace {
 
-// hwenou_advance by whole steps, one launch each (step1d.hip), on the caller's
-// stream: a kernel that resets the run's state, the wave speed of the initial
-// averages, the steps, and a kernel that brings the results home.  The state
-// alternates between the caller's arrays and the stage buffers.
-int advance_whole_steps(hwenou_handle* h, double* ubar, void* mom, const RunParams& R,
-                        double* t_out, int* steps_out) {
-  hipStream_t st = h->stream;
-  const int n = h->n_inst;
-  const size_t lines = (size_t)kAlphaStride * kAlphaSlots * n;
-  RunArgs r;
-  r.R = R;
-  r.run = h->d_run;
-  r.n_inst = n;
-  r.slots = h->step_slots;
-  r.nc = r.mom_planes = h->nc;
-  r.mom_elem = (int)h->mom_elem;
-  for (int b = 0; b < 2; ++b) {
-    r.st[b] = h->d_state + (size_t)b * n;
-    r.flag[b] = h->d_flag + (size_t)b * n;
-  }
-  for (int b = 0; b < 4; ++b) r.acc[b] = h->d_acc + b * lines;
-  r.last = 0;
-  r.u_odd = h->s1u;
-  r.m_odd = h->s1m;
-  r.u = ubar;
-  r.m = mom;
-  r.inst = h->d_inst;
-  r.plane = h->plane;
-  r.tiles = h->d_tiles;
-  r.n_tiles = h->n_tiles;
-  r.status = h->d_status;
-  r.t_host = h->h_t;
-  r.steps_host = h->h_steps;
-  r.status_host = h->h_status;
-  r.running_host = h->h_flags;
-  hipError_t e = launch_run_begin(r, st);
-  if (e != hipSuccess) return hip_fail(e, "run_begin launch");
-  AuxArgs a = aux_args(h, ubar);
-  a.alpha = r.acc[0];
-  a.alpha_stride = kAlphaStride * h->step_slots;
-  a.status = r.flag[0];
-  e = launch_max_wavespeed(a, st);
-  if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
+// Control record of the p-th step of a run: the buffers it reads and leaves.
+StepControl step_control(hwenou_handle* h, int p) {
+  const size_t n = h->n_inst, lines = n * h->slots * kAlphaStride;
+  StepControl c;
+  c.run = h->d_run;
+  c.st_in = h->d_state + (p & 1) * n;
+  c.st_out = h->d_state + ((p + 1) & 1) * n;
+  c.flag_in = h->d_flag + (p & 1) * n;
+  c.flag_out = h->d_flag + ((p + 1) & 1) * n;
+  c.acc_in = h->d_acc + (p & 3) * lines;
+  c.acc_out = h->d_acc + ((p + 1) & 3) * lines;
+  c.acc_zero = h->d_acc + ((p + 2) & 3) * lines;
+  c.slots = h->slots;
+  return c;
+}
 
+// The p-th step of a run as one launch; the state alternates between the
+// caller's arrays and a stage buffer.
+template <class TM>
+int whole_step(hwenou_handle* h, double* ubar, void* mom, int p, hipStream_t st) {
+  StepArgs<TM> A{};
+  A.P = scheme_params(h->desc);
+  A.ctl = step_control(h, p);
+  A.inst = h->d_inst;
+  A.u_in = p & 1 ? h->s1u : ubar;
+  A.m_in = static_cast<const TM*>(p & 1 ? h->s1m : mom);
+  A.u_out = p & 1 ? ubar : h->s1u;
+  A.m_out = static_cast<TM*>(p & 1 ? mom : h->s1m);
+  A.plane = h->plane;
+  A.tiles = h->d_tiles;
+  A.n_tiles = h->n_tiles;
+  A.n_waves = h->step_waves;
   const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
-  const SchemeParams P = scheme_params(h->desc);
-  auto step = [&](auto* tag, int p) {  // the p-th step of the run
-    using TM = std::remove_pointer_t<decltype(tag)>;
-    StepArgs<TM> A;
-    A.P = P;
-    A.inst = h->d_inst;
-    A.run = h->d_run;
-    A.u_in = p & 1 ? h->s1u : ubar;
-    A.m_in = static_cast<const TM*>(p & 1 ? h->s1m : mom);
-    A.u_out = p & 1 ? ubar : h->s1u;
-    A.m_out = static_cast<TM*>(p & 1 ? mom : h->s1m);
-    A.st_in = r.st[p & 1];
-    A.st_out = r.st[(p + 1) & 1];
-    A.flag_in = r.flag[p & 1];
-    A.flag_out = r.flag[(p + 1) & 1];
-    A.acc_in = r.acc[p & 3];
-    A.acc_out = r.acc[(p + 1) & 3];
-    A.acc_zero = r.acc[(p + 2) & 3];
-    A.slots = h->step_slots;
-    A.plane = h->plane;
-    A.tiles = h->d_tiles;
-    A.n_tiles = h->n_tiles;
-    A.n_waves = h->step_waves;
-    return launch_step_1d(h->desc.eq, chr, h->mixed, &A, h->step_waves, kStepThreads, st);
-  };
-  // Chunks of growing length; between them the device writes to a pinned slot
-  // whether any instance still runs, and the host waits only for the answer of
-  // the chunk before, so the device never idles.
-  int launched = 0, chunk = 64, slot = 0, prev = -1;
-  while (launched < R.max_steps) {
-    const int k = std::min(chunk, R.max_steps - launched);
-    for (int q = 0; q < k && e == hipSuccess; ++q)
-      e = h->mixed ? step(static_cast<float*>(nullptr), launched + q)
-                   : step(static_cast<double*>(nullptr), launched + q);
-    if (e != hipSuccess) break;
-    launched += k;
-    if (launched == R.max_steps) break;
-    r.last = launched & 1;
-    r.running_host = h->h_flags + slot;
-    if ((e = launch_run_poll(r, st)) != hipSuccess) break;
-    if ((e = hipEventRecord(h->ev_poll[slot], st)) != hipSuccess) break;
-    if (prev >= 0) {
-      if ((e = hipEventSynchronize(h->ev_poll[prev])) != hipSuccess) break;
-      if (!h->h_flags[prev]) break;
-    }
-    prev = slot;
-    slot ^= 1;
-    chunk = std::min(2 * chunk, 512);
+  const hipError_t e =
+      launch_step_1d(h->desc.eq, chr, h->mixed, &A, h->step_waves, kStepThreads, st);
+  return e == hipSuccess ? HWENOU_OK : hip_fail(e, "step kernel launch");
+}
+
+// The p-th step of a run: one launch, or one per stage with the last stage
+// writing into the caller's arrays.
+int launch_step(hwenou_handle* h, double* ubar, void* mom, int p, hipStream_t st) {
+  if (h->whole_steps)
+    return h->mixed ? whole_step<float>(h, ubar, mom, p, st)
+                    : whole_step<double>(h, ubar, mom, p, st);
+  const StepControl c = step_control(h, p);
+  if (h->dim == 1) {
+    const hipError_t e = launch_step_control(
+        {c, h->d_inst, h->n_inst, h->d_dt, h->d_alpha, h->d_done}, st);
+    if (e != hipSuccess) return hip_fail(e, "step_control launch");
   }
-  h->u_base = nullptr;
-  if (e != hipSuccess) return hip_fail(e, "step launch");
-  r.last = launched & 1;
-  if ((e = launch_run_end(r, st)) != hipSuccess) return hip_fail(e, "run_end launch");
-  HIPCHK(hipStreamSynchronize(st));
-  if (t_out) std::memcpy(t_out, h->h_t, n * sizeof(double));
-  if (steps_out) std::memcpy(steps_out, h->h_steps, n * sizeof(int));
-  for (int k = 0; k < n; ++k)
-    if (h->h_status[k] & 1) return HWENOU_ENONPHYSICAL;
+  h->u_base = ubar;
+  int rc = launch_stage(h, 0, h->d_dt, h->d_alpha, c, ubar, mom, h->s1u, h->s1m, st);
+  if (!rc) rc = launch_stage(h, 1, h->d_dt, h->d_alpha, c, h->s1u, h->s1m, h->s2u, h->s2m, st);
+  if (!rc) rc = launch_stage(h, 2, h->d_dt, h->d_alpha, c, h->s2u, h->s2m, ubar, mom, st);
+  return rc;
+}
+
+// The graph of kGraphSteps steps that start at a multiple of it.
+int capture_steps(hwenou_handle* h, double* ubar, void* mom) {
+  drop_graph(h);
+  HIPCHK(hipStreamBeginCapture(h->own, hipStreamCaptureModeThreadLocal));
+  int rc = HWENOU_OK;
+  for (int p = 0; p < kGraphSteps && !rc; ++p) rc = launch_step(h, ubar, mom, p, h->own);
+  hipError_t e = hipStreamEndCapture(h->own, &h->graph);
+  if (!rc && e != hipSuccess) rc = hip_fail(e, "hipStreamEndCapture");
+  if (!rc && (e = hipGraphInstantiate(&h->exec, h->graph, nullptr, nullptr, 0)) != hipSuccess) {
+    h->exec = nullptr;
+    rc = hip_fail(e, "hipGraphInstantiate");
+  }
+  if (rc) {
+    drop_graph(h);
+    return rc;
+  }
+  h->g_ubar = ubar;
+  h->g_mom = mom;
   return HWENOU_OK;
 }
 
@@ -878,114 +841,88 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
   if (!h || !ubar || !mom || !(cfl > 0.0) || !(t_final >= 0.0) || max_steps < 0)
     return HWENOU_EINVAL;
   if (!aligned(ubar, 8) || !aligned(mom, h->mom_elem)) return HWENOU_EINVAL;
-  if (h->work_dirty) {
-    int rc = build_work(h);
-    if (rc) return rc;
+  int rc = HWENOU_OK;
+  if (h->work_dirty && (rc = build_work(h))) return rc;
+  hipStream_t st = h->stream;
+  const int n = h->n_inst;
+  // a run begins with one kernel that resets its state, and the wave speed of
+  // the initial averages
+  RunArgs r{};
+  r.R = {cfl, t_final, max_steps};
+  r.run = h->d_run;
+  r.n_inst = n;
+  r.slots = h->slots;
+  r.nc = r.mom_planes = h->nc;
+  r.mom_elem = (int)h->mom_elem;
+  for (int b = 0; b < 2; ++b) {
+    r.st[b] = h->d_state + (size_t)b * n;
+    r.flag[b] = h->d_flag + (size_t)b * n;
   }
-  if (h->whole_steps)
-    return advance_whole_steps(h, ubar, mom, {cfl, t_final, max_steps}, t_out, steps_out);
-  hipStream_t st = h->own;
-  // order after the caller's prior work
-  HIPCHK(hipEventRecord(h->ev_in, h->stream));
-  HIPCHK(hipStreamWaitEvent(st, h->ev_in, 0));
-  // the previous call synchronised its stream, so the staging copy is free
-  h->h_run->cfl = cfl;
-  h->h_run->t_final = t_final;
-  h->h_run->max_steps = max_steps;
-  HIPCHK(hipMemcpyAsync(h->d_run, h->h_run, sizeof(RunParams), hipMemcpyHostToDevice, st));
-  HIPCHK(hipMemsetAsync(h->d_t, 0, h->n_inst * sizeof(double), st));
-  HIPCHK(hipMemsetAsync(h->d_steps, 0, h->n_inst * sizeof(int), st));
-  HIPCHK(hipMemsetAsync(h->d_done, 0, h->n_inst * sizeof(int), st));
-  HIPCHK(hipMemsetAsync(h->d_status, 0, h->n_inst * sizeof(int), st));
+  for (int b = 0; b < 4; ++b) r.acc[b] = h->d_acc + (size_t)b * n * h->slots * kAlphaStride;
+  r.last = 0;
+  r.u_odd = h->s1u;
+  r.m_odd = h->s1m;
+  r.u = ubar;
+  r.m = mom;
+  r.inst = h->d_inst;
+  r.plane = h->plane;
+  r.tiles = h->whole_steps ? h->d_tiles : nullptr;
+  r.n_tiles = h->n_tiles;
+  r.status = h->d_status;
+  r.t_host = h->h_t;
+  r.steps_host = h->h_steps;
+  r.status_host = h->h_status;
+  r.running_host = nullptr;
+  hipError_t e = launch_run_begin(r, st);
+  if (e != hipSuccess) return hip_fail(e, "run_begin launch");
   AuxArgs a = aux_args(h, ubar);
-  hipError_t e = launch_max_wavespeed(a, st);
+  a.alpha = r.acc[0];
+  a.alpha_stride = kAlphaStride * h->slots;
+  a.status = r.flag[0];
+  e = launch_max_wavespeed(a, st);
   if (e != hipSuccess) return hip_fail(e, "max_wavespeed launch");
-  // the first step's dt; later ones are set by the finish kernel of the step before
-  e = launch_dt(a, st);
-  if (e != hipSuccess) return hip_fail(e, "dt launch");
 
-  // whole steps (three stages and the finish kernel) as graphs, captured
-  // once and replayed by every later call on the same state arrays
-  if (h->exec[0] == nullptr || h->g_ubar != ubar || h->g_mom != mom) {
-    drop_graph(h);
-    for (int g = 0; g < 2; ++g) {
-      const int nsteps = g == 0 ? 1 : kMultiSteps;
-      hipGraph_t graph = nullptr;
-      HIPCHK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-      int rc = HWENOU_OK;
-      for (int q = 0; q < nsteps && rc == HWENOU_OK; ++q) {
-        rc = launch_stage(h, 0, h->d_dt, h->d_alpha, h->d_done, ubar, mom, h->s1u, h->s1m,
-                          nullptr, st);
-        if (rc) break;
-        h->u_base = ubar;
-        rc = launch_stage(h, 1, h->d_dt, h->d_alpha, h->d_done, h->s1u, h->s1m, h->s2u, h->s2m,
-                          nullptr, st);
-        if (rc) break;
-        rc = launch_stage(h, 2, h->d_dt, h->d_alpha, h->d_done, h->s2u, h->s2m, ubar, mom,
-                          h->d_alpha_next, st);
-        if (rc) break;
-        if ((e = launch_finish(a, st)) != hipSuccess) rc = hip_fail(e, "finish launch");
-      }
-      e = hipStreamEndCapture(st, &graph);
-      if (rc) {
-        if (graph) (void)hipGraphDestroy(graph);
-        drop_graph(h);
-        return rc;
-      }
-      if (e != hipSuccess) {
-        drop_graph(h);
-        return hip_fail(e, "hipStreamEndCapture");
-      }
-      e = hipGraphInstantiate(&h->exec[g], graph, nullptr, nullptr, 0);
-      h->graph[g] = graph;
-      if (e != hipSuccess) {
-        h->exec[g] = nullptr;
-        drop_graph(h);
-        return hip_fail(e, "hipGraphInstantiate");
-      }
-    }
-    h->g_ubar = ubar;
-    h->g_mom = mom;
-  }
-  // Replays in chunks of growing length (multi-step graphs, then single
-  // steps for the rest of a chunk).  After each chunk the all-done flag is
-  // copied to a pinned slot; the host waits only for the flag of the chunk
-  // before, so the device never idles between chunks.  Steps replayed after
-  // every instance is done are no-ops.
-  int launched = 0, chunk = 2 * kMultiSteps, slot = 0, prev = -1;
-  while (launched < max_steps && e == hipSuccess) {
+  // Steps in chunks of growing length.  Between chunks the device writes to a
+  // pinned slot whether any instance runs on, and the host waits only for the
+  // answer of the chunk before, so the device never idles.  Steps after every
+  // instance is done are no-ops.
+  int launched = 0, chunk = 64, slot = 0, prev = -1;
+  while (launched < max_steps && !rc) {
     const int k = std::min(chunk, max_steps - launched);
-    for (int r = 0; r + kMultiSteps <= k && e == hipSuccess; r += kMultiSteps)
-      e = hipGraphLaunch(h->exec[1], st);
-    for (int r = 0; r < k % kMultiSteps && e == hipSuccess; ++r) e = hipGraphLaunch(h->exec[0], st);
-    if (e != hipSuccess) break;
-    launched += k;
-    e = hipMemcpyAsync(&h->h_flags[slot], h->d_all_done, sizeof(int), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipEventRecord(h->ev_poll[slot], st);
-    if (e != hipSuccess) break;
-    if (prev >= 0) {
-      e = hipEventSynchronize(h->ev_poll[prev]);
-      if (e != hipSuccess || h->h_flags[prev]) break;
+    int q = 0;
+    if (!h->whole_steps && k >= kGraphSteps) {
+      if (h->exec == nullptr || h->g_ubar != ubar || h->g_mom != mom)
+        rc = capture_steps(h, ubar, mom);
+      for (; q + kGraphSteps <= k && !rc; q += kGraphSteps)
+        if ((e = hipGraphLaunch(h->exec, st)) != hipSuccess) rc = hip_fail(e, "graph replay");
     }
+    for (; q < k && !rc; ++q) rc = launch_step(h, ubar, mom, launched + q, st);
+    if (rc) break;
+    launched += k;
+    if (launched == max_steps) break;
+    r.last = launched & 1;
+    r.running_host = h->h_running + slot;
+    if ((e = launch_run_poll(r, st)) == hipSuccess) e = hipEventRecord(h->ev_poll[slot], st);
+    if (e == hipSuccess && prev >= 0) e = hipEventSynchronize(h->ev_poll[prev]);
+    if (e != hipSuccess) {
+      rc = hip_fail(e, "poll");
+      break;
+    }
+    if (prev >= 0 && !h->h_running[prev]) break;
     prev = slot;
     slot ^= 1;
     chunk = std::min(2 * chunk, 512);
   }
   h->u_base = nullptr;  // the steps' stage-0 launches overwrote the stored v^n
-  if (e != hipSuccess) return hip_fail(e, "graph replay");
+  if (rc) return rc;
+  // and ends with one that brings its results home
+  r.last = launched & 1;
+  if ((e = launch_run_end(r, st)) != hipSuccess) return hip_fail(e, "run_end launch");
   HIPCHK(hipStreamSynchronize(st));
-  std::vector<double> t(h->n_inst);
-  std::vector<int> steps(h->n_inst), status(h->n_inst);
-  HIPCHK(hipMemcpy(t.data(), h->d_t, h->n_inst * sizeof(double), hipMemcpyDeviceToHost));
-  HIPCHK(hipMemcpy(steps.data(), h->d_steps, h->n_inst * sizeof(int), hipMemcpyDeviceToHost));
-  HIPCHK(hipMemcpy(status.data(), h->d_status, h->n_inst * sizeof(int), hipMemcpyDeviceToHost));
-  if (t_out) std::memcpy(t_out, t.data(), h->n_inst * sizeof(double));
-  if (steps_out) std::memcpy(steps_out, steps.data(), h->n_inst * sizeof(int));
-  // later work on the caller's stream sees the result
-  HIPCHK(hipEventRecord(h->ev_out, st));
-  HIPCHK(hipStreamWaitEvent(h->stream, h->ev_out, 0));
-  for (int k = 0; k < h->n_inst; ++k)
-    if (status[k] & 1) return HWENOU_ENONPHYSICAL;
+  if (t_out) std::memcpy(t_out, h->h_t, n * sizeof(double));
+  if (steps_out) std::memcpy(steps_out, h->h_steps, n * sizeof(int));
+  for (int k = 0; k < n; ++k)
+    if (h->h_status[k] & 1) return HWENOU_ENONPHYSICAL;
   return HWENOU_OK;
 }
 

@@ -604,6 +604,14 @@ __device__ __forceinline__ double from_next(double x) {
   return __longlong_as_double(((long long)h2 << 32) | (unsigned int)l2);
 }
 
+// A value that is the same on every lane, moved to scalar registers.
+__device__ __forceinline__ double uniform(double x) {
+  const long long b = __double_as_longlong(x);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((int)b);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | lo);
+}
+
 // wave-wide max of a non-negative double (64 lanes)
 __device__ __forceinline__ double wave_max(double x) {
 #pragma unroll

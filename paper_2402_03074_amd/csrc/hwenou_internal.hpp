@@ -9,6 +9,24 @@
 
 namespace hwenou {
 
+// A read of data that no kernel writes while its kernel runs (the work
+// list, the instance records, alpha and dt, what the step before left), through the
+// constant address space and word by word, so that at a wave-uniform address
+// it becomes a scalar load, which does not wait behind the wave's vector
+// memory traffic.
+template <class T>
+__device__ __forceinline__ T load_invariant(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "records of whole 32-bit words");
+  using Word = const __attribute__((address_space(4))) unsigned;
+  Word* q = (Word*)p;
+  unsigned v[sizeof(T) / 4];
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) v[k] = q[k];
+  T r;
+  __builtin_memcpy(&r, v, sizeof(T));
+  return r;
+}
+
 // One problem instance as the kernels see it.
 struct InstDev {
   int nx, ny;        // cells (ny = 1 in 1D)
@@ -32,10 +50,10 @@ constexpr int kStripWidth = 62;
 // index picks one), so that ~1000 waves ending together on one instance do
 // not all serialise their atomics on one address.  Each accumulator (x and y
 // wave speed) sits in a 128-byte line of its own (kAlphaStride doubles),
-// since the atomics of one line are serialised as well; the finish kernel
-// takes the maximum of the slots.  Handles of many instances use fewer slots
-// per instance: few waves end on any one instance at a time, and the finish
-// kernel's loop over the slots grows with their number.
+// since the atomics of one line are serialised as well; the next step takes
+// the maximum of the slots.  Handles of many instances use fewer slots per
+// instance: few waves end on any one instance at a time, and every wave of the
+// next step reads all slots.
 constexpr int kAlphaSlots = 16;
 constexpr int kAlphaStride = 16;
 __device__ __host__ __forceinline__ int alpha_slot(int inst, int wave, int slots) {
@@ -60,44 +78,16 @@ struct StepState {
   int steps, done;
 };
 
-// What one step of an instance starts from: its time step and wave speed, or
-// that it is done.  It is when it has reached t_final or max_steps, or a
-// kernel has flagged one of its states as non-physical or non-finite (it
-// stops after the step that failed, and its t and step count say where), or
-// its wave speed is infinite (failed: to be flagged now).  The same rule as
-// set_step of the one-stage path.
-struct StepDt {
-  double dt, alpha;
-  bool done, failed;
-};
-__device__ __forceinline__ StepDt step_dt(const RunParams& R, double dx, const StepState& s,
-                                          int flag, double ax) {
-  StepDt r;
-  r.alpha = ax;
-  r.dt = 0.0;
-  r.failed = false;
-  r.done = s.done || flag || s.steps >= R.max_steps || s.t >= R.t_final * (1.0 - 1e-14);
-  if (r.done) return r;
-  if (!isfinite(ax)) {
-    r.done = r.failed = true;
-    return r;
-  }
-  // zero wave speed: every flux vanishes, the CFL bound is infinite
-  r.dt = ax == 0.0 ? R.t_final - s.t : R.cfl * dx / ax;
-  if (s.t + r.dt > R.t_final) r.dt = R.t_final - s.t;
-  return r;
-}
-
-template <class TM>
-struct StepArgs {
-  SchemeParams P;
-  const InstDev* inst;
-  const RunParams* run;
-  const double* u_in;
-  const TM* m_in;
-  double* u_out;
-  TM* m_out;
-  const StepState* st_in;  // [n_inst], written by the step before
+// The state of a run (one hwenou_advance call) that its kernels carry from
+// step to step.  Time, step count, completion and failure flags alternate
+// between two buffers, the wave-speed accumulators between four: every kernel
+// of step p forms its instances' time step itself from what step p - 1 left,
+// so that no wave reads what another wave of the same step writes, and a step
+// has no kernel of its own for its bookkeeping.  One wave per instance writes
+// the new time and step count and clears the accumulators of the next step.
+struct StepControl {
+  const RunParams* run;    // nullptr: the caller gives dt and alpha (hwenou_stage)
+  const StepState* st_in;  // [n_inst]
   StepState* st_out;
   const int* flag_in;      // [n_inst]: non-physical states found before this step
   int* flag_out;           // [n_inst]: ... and by this step
@@ -105,6 +95,88 @@ struct StepArgs {
   double* acc_out;         // wave speeds of the output (cleared by the step before)
   double* acc_zero;        // accumulators to clear for the next step
   int slots;
+};
+
+// What one step of an instance starts from: its time step and wave speeds, or
+// that it is done.  It is when it has reached t_final or max_steps, or a
+// kernel has flagged one of its states as non-physical or non-finite (it
+// stops after the step that failed, and its t and step count say where), or
+// its wave speed is infinite (failed: to be flagged now).  The wave speeds are
+// reduced with fmax, which drops NaN arguments, so a NaN state is caught by
+// the flag, not by the wave speed.
+struct StepDt {
+  double dt, ax, ay;
+  StepState s;
+  bool done, failed;
+};
+template <int DIM>
+__device__ __forceinline__ StepDt step_dt(const StepControl& A, int inst, const InstDev& I) {
+  StepDt r;
+  const RunParams R = load_invariant(A.run);
+  const StepState s = load_invariant(A.st_in + inst);
+  const int flag = load_invariant(A.flag_in + inst);
+  struct Line {
+    double x, y;
+  };
+  const double* acc = A.acc_in + kAlphaStride * inst * A.slots;
+  if (A.slots == 1) {
+    const Line l = load_invariant(reinterpret_cast<const Line*>(acc));
+    r.ax = l.x;
+    r.ay = l.y;
+  } else {
+    // all slot lines in one round of loads; the last one stands in for those
+    // beyond this handle's slots
+    Line l[kAlphaSlots];
+#pragma unroll
+    for (int q = 0; q < kAlphaSlots; ++q)
+      l[q] = load_invariant(
+          reinterpret_cast<const Line*>(acc + kAlphaStride * min(q, A.slots - 1)));
+    r.ax = r.ay = 0.0;
+#pragma unroll
+    for (int q = 0; q < kAlphaSlots; ++q) {
+      r.ax = fmax(r.ax, l[q].x);
+      if (DIM == 2) r.ay = fmax(r.ay, l[q].y);
+    }
+  }
+  r.s = s;
+  r.dt = 0.0;
+  r.failed = false;
+  r.done = s.done || flag || s.steps >= R.max_steps || s.t >= R.t_final * (1.0 - 1e-14);
+  if (r.done) return r;
+  if (!isfinite(r.ax) || (DIM == 2 && !isfinite(r.ay))) {
+    r.done = r.failed = true;
+    return r;
+  }
+  if (r.ax == 0.0 && (DIM == 1 || r.ay == 0.0))
+    r.dt = R.t_final - s.t;  // zero wave speed: every flux vanishes, the CFL bound is infinite
+  else if (DIM == 1)
+    r.dt = R.cfl * I.dx / r.ax;
+  else
+    r.dt = R.cfl / (r.ax / I.dx + r.ay / I.dy);
+  if (s.t + r.dt > R.t_final) r.dt = R.t_final - s.t;
+  return r;
+}
+
+// Done by one lane per instance and step.
+__device__ __forceinline__ void write_step(const StepControl& A, int inst, const StepDt& d) {
+  A.st_out[inst] = {d.done ? d.s.t : d.s.t + d.dt, d.done ? d.s.steps : d.s.steps + 1,
+                    d.done ? 1 : 0};
+  if (d.failed) atomicOr(A.flag_out + inst, 1);
+  for (int q = 0; q < A.slots; ++q) {
+    double* line = A.acc_zero + kAlphaStride * (inst * A.slots + q);
+    line[0] = line[1] = 0.0;
+  }
+}
+
+template <class TM>
+struct StepArgs {
+  SchemeParams P;
+  StepControl ctl;
+  const InstDev* inst;
+  const double* u_in;
+  const TM* m_in;
+  double* u_out;
+  TM* m_out;
   long long plane;
   const TileItem* tiles;
   int n_tiles, n_waves;    // wave w takes tiles [n_tiles w / n_waves, n_tiles (w+1) / n_waves)
@@ -114,19 +186,18 @@ template <class TM>
 struct StageArgs {
   SchemeParams P;
   const InstDev* inst;
-  const double* dt;     // [n_inst]
-  const double* alpha;  // [n_inst][2]
-  const int* done;      // [n_inst] or nullptr
+  StepControl ctl;      // ctl.run == nullptr: not part of a run
+  const double* dt;     // [n_inst], read outside a run and by the 1D kernels
+  const double* alpha;  // [n_inst][2], likewise
+  const int* done;      // [n_inst] or nullptr (1D kernels)
   const double* u_in;   // [nc][plane]
   const TM* m_in;       // [dim][nc][plane]
   const double* u_base; // u^n for stages 1, 2
   TM* m_base;           // v^_n (and w^_n): written by stage 0, read by stages 1, 2
   double* u_out;
   TM* m_out;
-  double* alpha_next;   // [n_inst][alpha_slots][kAlphaStride] or nullptr: max wave speed of
-                        // the output (x, y in the first two doubles of each slot)
-  int alpha_slots;      // accumulators per instance (power of two, <= kAlphaSlots)
   int* status;          // [n_inst]: set to 1 on a non-physical or non-finite output
+                        // (ctl.flag_out within a run)
   long long plane;      // cells per component plane
   const WorkItem* work;
   const int* work_ptr;  // wave w handles work[work_ptr[w] .. work_ptr[w+1])
@@ -181,21 +252,22 @@ struct AuxArgs {
   int alpha_stride;
   double* part;          // [n_inst][part_blocks][2] partial maxima
   int part_blocks;       // speed_blocks of the largest instance
-  double* dt;            // [n_inst]
-  double* t;             // [n_inst]
-  int* steps;            // [n_inst]
-  int* done;             // [n_inst]
   int* status;           // [n_inst]: 1 once the instance left the physical states
-  double* alpha_next;    // [n_inst][alpha_slots][kAlphaStride]
-  int alpha_slots;
-  const RunParams* run;  // CFL number, final time, step limit
-  int* all_done;         // 1 when every instance is done
 };
 hipError_t launch_max_wavespeed(const AuxArgs& a, hipStream_t s);
-hipError_t launch_dt(const AuxArgs& a, hipStream_t s);
-hipError_t launch_finish(const AuxArgs& a, hipStream_t s);
 
-// Start and end of a run of whole 1D steps.
+// One step's time steps, wave speeds and completion into arrays, for the 1D
+// kernels that run one stage per launch.
+struct ControlArgs {
+  StepControl ctl;
+  const InstDev* inst;
+  int n_inst;
+  double *dt, *alpha;
+  int* done;
+};
+hipError_t launch_step_control(const ControlArgs& a, hipStream_t s);
+
+// Start, polls and end of a run.
 struct RunArgs {
   RunParams R;
   RunParams* run;          // device copy of R
@@ -204,7 +276,7 @@ struct RunArgs {
   int* flag[2];
   double* acc[4];
   int last;                // buffer (0, 1) the last step wrote
-  // end of the run
+  // whole 1D steps (tiles != nullptr): what brings the state home
   const double* u_odd;     // scratch state that odd steps write
   const void* m_odd;
   double* u;

@@ -171,16 +171,13 @@ extern "C" int hwenou_step_noalloc(const hwenou_desc* d, const hwenou_inst* inst
   const SchemeParams P = scheme_params(*d);
   auto run = [&](auto* tag) -> hipError_t {
     using TM = std::remove_pointer_t<decltype(tag)>;
-    StageArgs<TM> A;
+    StageArgs<TM> A{};  // not part of a run: no control record, no done flags
     A.P = P;
     A.inst = reinterpret_cast<const InstDev*>(base + kOffInst);
     A.dt = dt_dev;
     A.alpha = alpha_dev;
-    A.done = nullptr;
     A.u_base = ubar;
     A.m_base = static_cast<TM*>(m_base);
-    A.alpha_next = nullptr;
-    A.alpha_slots = 1;
     A.status = status;
     A.plane = cells;
     A.work = reinterpret_cast<const WorkItem*>(base + off_items);

@@ -121,10 +121,10 @@ __global__ __launch_bounds__(256, (min_waves_1d<EQ, CHAR, TR>())) void stage1d_k
       }
     }
 
+    const double idx = 1.0 / I.dx;
     double F1[NC];
     TR F2[NC], vh[NC];
-    const double idx = 1.0 / I.dx;
-    cell_rhs_1d<EQ, CHAR, TR, NC>(P, Um, Uc, Up, Vm, Vp, (TR)alpha_in, idx, F1, F2, vh);
+#include "tile1d_terms.inc"
 
     // ---- RK combination ----
     double Uo[NC];
@@ -149,15 +149,15 @@ __global__ __launch_bounds__(256, (min_waves_1d<EQ, CHAR, TR>())) void stage1d_k
     double sx = 0.0, sy = 0.0;
     bool ok = true;
     if (owner) {
-      if (ST == 2 && A.alpha_next != nullptr)  // the wave speeds feed the next step's alpha
+      if (ST == 2 && A.ctl.run != nullptr)  // the wave speeds feed the next step's alpha
         ok = wave_speeds<EQ, NC>(P, Uo, sx, sy);
       else
         ok = physical_state<EQ, NC>(Uo);
     }
     if (!ok) atomicOr(&A.status[wk.inst], 1);
-    if (ST == 2 && A.alpha_next != nullptr) {
+    if (ST == 2 && A.ctl.run != nullptr) {
       const double mx = wave_max(owner ? sx : 0.0);
-      if (lane == 0) atomic_max_nonneg(A.alpha_next + alpha_slot(wk.inst, w, A.alpha_slots), mx);
+      if (lane == 0) atomic_max_nonneg(A.ctl.acc_out + alpha_slot(wk.inst, w, A.ctl.slots), mx);
     }
   }
 }

@@ -451,10 +451,24 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
   const long long plane = A.plane;
   const double gm1 = P.gas_gamma - 1.0;
 
-  for (int it = A.work_ptr[w]; it < A.work_ptr[w + 1]; ++it) {
-    const WorkItem wk = A.work[it];
-    if (A.done != nullptr && A.done[wk.inst]) continue;
-    const InstDev I = A.inst[wk.inst];
+  // the work list and the records of a run's instance are scalar loads
+  const int it_end = load_invariant(A.work_ptr + w + 1);
+  for (int it = load_invariant(A.work_ptr + w); it < it_end; ++it) {
+    const WorkItem wk = load_invariant(A.work + it);
+    const InstDev I = load_invariant(A.inst + wk.inst);
+    double dt, alpha_x, alpha_y;
+    if (A.ctl.run == nullptr) {
+      dt = load_invariant(A.dt + wk.inst);
+      alpha_x = load_invariant(A.alpha + 2 * wk.inst);
+      alpha_y = load_invariant(A.alpha + 2 * wk.inst + 1);
+    } else {
+      const StepDt d = step_dt<2>(A.ctl, wk.inst, I);
+      if (ST == 2 && wk.a == 0 && wk.b == 0 && lane == 0) write_step(A.ctl, wk.inst, d);
+      if (d.done) continue;
+      dt = uniform(d.dt);
+      alpha_x = uniform(d.ax);
+      alpha_y = uniform(d.ay);
+    }
     const int nx = I.nx, ny = I.ny;
     const int c0 = wk.a * kStripWidth;
     int i = c0 - 1 + lane;
@@ -464,9 +478,8 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
     // that loads need no lane mask; only owners store)
     const int ic = min(max(i, 0), nx - 1);
     const unsigned ou = (unsigned)ic * 8u, om = (unsigned)ic * (unsigned)sizeof(TM);
-    const TR a1 = (TR)A.alpha[2 * wk.inst], a2 = (TR)A.alpha[2 * wk.inst + 1];
-    const double dt = A.dt[wk.inst];
-    const double idx = 1.0 / I.dx, idy = 1.0 / I.dy;
+    const TR a1 = (TR)alpha_x, a2 = (TR)alpha_y;
+    const double idx = uniform(1.0 / I.dx), idy = uniform(1.0 / I.dy);
     const int r0 = wk.b, r1 = wk.c;
     const double* u_in = A.u_in + I.offset;
     const TM* m_in = A.m_in + I.offset;
@@ -638,7 +651,7 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) U5[k] = B.u[sc][k][lane + 1];
         pr = make_prim<TR>(gm1, U5);
-        char_sweep<SPLIT ? 1 : 0, SI, SPLIT, SPLIT, TR, TM, SPLIT && sizeof(TR) == 8>(
+        char_sweep<SPLIT ? 1 : 0, SI, SPLIT, SPLIT, TR, TM, SPLIT && SI && sizeof(TR) == 8>(
             P, pr, B, sb, sc, st, lane, Cc, c1buf, pbuf, false);
       } else {
 #pragma unroll
@@ -804,7 +817,7 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
           pr = make_prim<TR>(gm1, U5);
         }
         if constexpr (SPLIT)
-          char_sweep<0, SI, false, !IFACE, TR, TM, !IFACE && sizeof(TR) == 8>(P, pr, B, sb, sc, st, lane,
+          char_sweep<0, SI, false, !IFACE, TR, TM, !IFACE && SI && sizeof(TR) == 8>(P, pr, B, sb, sc, st, lane,
                                                                       Cc, c1buf, pbuf, true);
         double F1x[NC];
         TR F2x[NC], F3x[NC];
@@ -874,10 +887,10 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
       st = s0;
     }
     if (!ok) atomicOr(&A.status[wk.inst], 1);
-    if (ST == 2 && A.alpha_next != nullptr) {
+    if (ST == 2 && A.ctl.run != nullptr) {
       const double mx = wave_max(amax_x), my = wave_max(amax_y);
       if (lane == 0) {
-        double* acc = A.alpha_next + alpha_slot(wk.inst, blockIdx.x, A.alpha_slots);
+        double* acc = A.ctl.acc_out + alpha_slot(wk.inst, blockIdx.x, A.ctl.slots);
         atomic_max_nonneg(acc, mx);
         atomic_max_nonneg(acc + 1, my);
       }

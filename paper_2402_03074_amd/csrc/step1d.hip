@@ -25,14 +25,6 @@
 // stage.  An instance with exactly one periodic side has no such rule (its
 // wrapped cells depend on the other side's ghost cells) and runs one stage per
 // launch.
-//
-// Per-instance state (t, step count, done) and the failure flags alternate
-// between two buffers from step to step, the wave-speed accumulators between
-// four: a step reads what the step before it left, so no wave of a launch
-// reads what another wave of the same launch writes.  Every wave forms the
-// time step of its tile's instance itself; the wave of the instance's first
-// tile writes the new t and step count and clears the accumulators that the
-// next step will fill.
 #include <algorithm>
 
 #include "tile1d.hpp"
@@ -47,9 +39,18 @@ constexpr int min_waves_step1d() {
   return EQ == EQ_EULER ? 3 : 1;
 }
 
+template <int EQ, bool CHAR, class TR, int NC>
+__device__ __forceinline__ void cell_rhs_1d(const SchemeParams& P, const double (&Um)[NC],
+                                            const double (&Uc)[NC], const double (&Up)[NC],
+                                            const double (&Vm)[NC], const double (&Vp)[NC],
+                                            TR alpha_in, double idx, double (&F1)[NC],
+                                            TR (&F2)[NC], TR (&vh)[NC]) {
+#include "tile1d_terms.inc"
+}
+
 // Everything one stage of a tile needs from one lane to the next.
 template <int EQ, bool CHAR, int ST, class TR, class TM, int NC>
-__device__ __forceinline__ void rk_stage(const SchemeParams& P, TR alpha, double idx, double dt,
+__device__ __forceinline__ void rk_stage(const SchemeParams& P, double alpha_in, double idx, double dt,
                                          const double (&Uend)[NC], const TM (&Vend)[NC],
                                          bool edge_lo, bool edge_hi, double (&Uc)[NC],
                                          TM (&Vc)[NC], double (&Ub)[NC], TM (&Mb)[NC]) {
@@ -75,7 +76,7 @@ __device__ __forceinline__ void rk_stage(const SchemeParams& P, TR alpha, double
   }
   double F1[NC];
   TR F2[NC], vh[NC];
-  cell_rhs_1d<EQ, CHAR, TR, NC>(P, Um, Uc, Up, Vm, Vp, alpha, idx, F1, F2, vh);
+  cell_rhs_1d<EQ, CHAR, TR, NC>(P, Um, Uc, Up, Vm, Vp, (TR)alpha_in, idx, F1, F2, vh);
 #pragma unroll
   for (int k = 0; k < NC; ++k) {
     const double ub = ST == 0 ? 0.0 : Ub[k];
@@ -119,7 +120,6 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
   if (w >= A.n_waves) return;
   const SchemeParams& P = A.P;
   const long long plane = A.plane;
-  const RunParams R = load_invariant(A.run);
 
   // contiguous run of tiles
   const int it0 = (int)((long long)A.n_tiles * w / A.n_waves);
@@ -127,14 +127,15 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
   int inst = -1;
   InstDev I;
   StepDt sd;
+  double dt = 0.0, alpha_in = 0.0, idx = 0.0;
   double mx = 0.0;   // wave speed of this wave's output cells of `inst`
   bool ok = true;
   auto flush = [&]() {  // hand over what the wave knows about instance `inst`
     if (inst < 0 || sd.done) return;
     const double m = wave_max_dpp(mx);
     if (lane == 63)
-      atomic_max_nonneg(A.acc_out + alpha_slot(inst, w, A.slots), m);
-    if (!ok) atomicOr(A.flag_out + inst, 1);
+      atomic_max_nonneg(A.ctl.acc_out + alpha_slot(inst, w, A.ctl.slots), m);
+    if (!ok) atomicOr(A.ctl.flag_out + inst, 1);
     mx = 0.0;
     ok = true;
   };
@@ -144,38 +145,15 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
       flush();
       inst = wk.inst;
       I = load_invariant(A.inst + inst);
-      const StepState s = load_invariant(A.st_in + inst);
-      const int flag = load_invariant(A.flag_in + inst);
-      double ax = 0.0;
-      const double* acc = A.acc_in + kAlphaStride * inst * A.slots;
-      if (A.slots == 1) {
-        ax = load_invariant(acc);
-      } else {
-        // all slot lines in one round of loads; the last one stands in for
-        // those beyond this handle's slots
-        double a[kAlphaSlots];
-#pragma unroll
-        for (int q = 0; q < kAlphaSlots; ++q)
-          a[q] = load_invariant(acc + kAlphaStride * min(q, A.slots - 1));
-#pragma unroll
-        for (int q = 0; q < kAlphaSlots; ++q) ax = fmax(ax, a[q]);
-      }
-      sd = step_dt(R, I.dx, s, flag, ax);
-      if (wk.start == 0 && lane == 0) {
-        StepState o;
-        o.t = sd.done ? s.t : s.t + sd.dt;
-        o.steps = sd.done ? s.steps : s.steps + 1;
-        o.done = sd.done ? 1 : 0;
-        A.st_out[inst] = o;
-        if (sd.failed) atomicOr(A.flag_out + inst, 1);
-        for (int q = 0; q < A.slots; ++q)
-          A.acc_zero[kAlphaStride * (inst * A.slots + q)] = 0.0;
-      }
+      sd = step_dt<1>(A.ctl, inst, I);
+      dt = uniform(sd.dt);
+      alpha_in = uniform(sd.ax);
+      idx = uniform(1.0 / I.dx);
+      if (wk.start == 0 && lane == 0) write_step(A.ctl, inst, sd);
     }
     if (sd.done) continue;
     const int n = I.nx;
     const bool periodic = I.bc[0] == BC_PERIODIC;
-    const double idx = 1.0 / I.dx;
     // Cell of this lane, and the cell it reads.  Lanes further out than any
     // valid result reaches read some cell of the instance: past the last one
     // periodic lanes stop at n + 5, the others at the two ghost cells that
@@ -226,16 +204,15 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
     const bool ghosts = !periodic && (wk.start < 5 || wk.start + 58 >= n);
     const int src = min(max(ic - wk.start + 5, 0), 63);
 
-    const TR alpha = (TR)sd.alpha;
-    rk_stage<EQ, CHAR, 0, TR, TM, NC>(P, alpha, idx, sd.dt, Uend, Vend, edge_lo, edge_hi, Uc, Vc,
+    rk_stage<EQ, CHAR, 0, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, edge_lo, edge_hi, Uc, Vc,
                                       Ub, Mb);
     if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
     if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
-    rk_stage<EQ, CHAR, 1, TR, TM, NC>(P, alpha, idx, sd.dt, Uend, Vend, false, false, Uc, Vc, Ub,
+    rk_stage<EQ, CHAR, 1, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
                                       Mb);
     if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
     if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
-    rk_stage<EQ, CHAR, 2, TR, TM, NC>(P, alpha, idx, sd.dt, Uend, Vend, false, false, Uc, Vc, Ub,
+    rk_stage<EQ, CHAR, 2, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
                                       Mb);
     if (owner) {
       const long long o = I.offset + i;
