@@ -77,6 +77,9 @@ struct hwenou_handle {
   // two periodic sides or none
   bool whole_steps = false;
   int n_tiles = 0, step_waves = 0;
+  // runs of whole steps in one launch, a block of this many waves per instance
+  // (0: not for this handle)
+  int block_waves = 0;
   // work lists
   int waves_per_cu = 0, rows_per_item = 0;
   int n_cu = 256;
@@ -535,6 +538,15 @@ int hwenou_create(const hwenou_desc* d, int n_inst, const hwenou_inst* inst, voi
     for (int k = 0; k < n_inst; ++k)
       for (int s = 0; s < inst[k].nx; s += kStepWidth) tiles.push_back({k, s});
   h->n_tiles = (int)tiles.size();
+  // One block per instance where a block can hold the largest and every block
+  // has a CU of its own: beyond that a launch per step spreads the tiles of
+  // uneven instances more evenly.
+  if (h->whole_steps && n_inst <= h->n_cu) {
+    int most = 0;
+    for (int k = 0; k < n_inst; ++k)
+      most = std::max(most, (inst[k].nx + kStepWidth - 1) / kStepWidth);
+    if (most <= block_run_waves(d->eq)) h->block_waves = most;
+  }
   for (int k = 0; k < n_inst; ++k)
     h->part_blocks = std::max(
         h->part_blocks, speed_blocks((long long)inst[k].nx * (d->dim == 1 ? 1 : inst[k].ny),
@@ -792,6 +804,28 @@ int whole_step(hwenou_handle* h, double* ubar, void* mom, int p, hipStream_t st)
   return e == hipSuccess ? HWENOU_OK : hip_fail(e, "step kernel launch");
 }
 
+// Up to `steps` steps of a run in one launch, the state held by one block per
+// instance from step to step; the run's state stays in its first buffers.
+template <class TM>
+int block_run(hwenou_handle* h, double* ubar, void* mom, int steps, hipStream_t st) {
+  BlockRunArgs<TM> A{};
+  A.P = scheme_params(h->desc);
+  A.inst = h->d_inst;
+  A.run = h->d_run;
+  A.u = ubar;
+  A.m = static_cast<TM*>(mom);
+  A.st = h->d_state;
+  A.flag = h->d_flag;
+  A.acc = h->d_acc;
+  A.plane = h->plane;
+  A.n_inst = h->n_inst;
+  A.steps = steps;
+  const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
+  const hipError_t e =
+      launch_block_run_1d(h->desc.eq, chr, h->mixed, &A, h->n_inst, h->block_waves, st);
+  return e == hipSuccess ? HWENOU_OK : hip_fail(e, "run kernel launch");
+}
+
 // The p-th step of a run: one launch, or one per stage with the last stage
 // writing into the caller's arrays.
 int launch_step(hwenou_handle* h, double* ubar, void* mom, int p, hipStream_t st) {
@@ -866,7 +900,7 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
   r.m = mom;
   r.inst = h->d_inst;
   r.plane = h->plane;
-  r.tiles = h->whole_steps ? h->d_tiles : nullptr;
+  r.tiles = h->whole_steps && !h->block_waves ? h->d_tiles : nullptr;
   r.n_tiles = h->n_tiles;
   r.status = h->d_status;
   r.t_host = h->h_t;
@@ -886,11 +920,14 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
   // pinned slot whether any instance runs on, and the host waits only for the
   // answer of the chunk before, so the device never idles.  Steps after every
   // instance is done are no-ops.
-  int launched = 0, chunk = 64, slot = 0, prev = -1;
+  int launched = 0, chunk = h->block_waves ? 1024 : 64, slot = 0, prev = -1;
   while (launched < max_steps && !rc) {
     const int k = std::min(chunk, max_steps - launched);
     int q = 0;
-    if (!h->whole_steps && k >= kGraphSteps) {
+    if (h->block_waves) {
+      rc = h->mixed ? block_run<float>(h, ubar, mom, k, st) : block_run<double>(h, ubar, mom, k, st);
+      q = k;
+    } else if (!h->whole_steps && k >= kGraphSteps) {
       if (h->exec == nullptr || h->g_ubar != ubar || h->g_mom != mom)
         rc = capture_steps(h, ubar, mom);
       for (; q + kGraphSteps <= k && !rc; q += kGraphSteps)
@@ -900,7 +937,7 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
     if (rc) break;
     launched += k;
     if (launched == max_steps) break;
-    r.last = launched & 1;
+    r.last = h->block_waves ? 0 : launched & 1;
     r.running_host = h->h_running + slot;
     if ((e = launch_run_poll(r, st)) == hipSuccess) e = hipEventRecord(h->ev_poll[slot], st);
     if (e == hipSuccess && prev >= 0) e = hipEventSynchronize(h->ev_poll[prev]);
@@ -911,12 +948,12 @@ int hwenou_advance(hwenou_handle* h, double* ubar, void* mom, double cfl, double
     if (prev >= 0 && !h->h_running[prev]) break;
     prev = slot;
     slot ^= 1;
-    chunk = std::min(2 * chunk, 512);
+    chunk = std::min(2 * chunk, h->block_waves ? 4096 : 512);
   }
   h->u_base = nullptr;  // the steps' stage-0 launches overwrote the stored v^n
   if (rc) return rc;
   // and ends with one that brings its results home
-  r.last = launched & 1;
+  r.last = h->block_waves ? 0 : launched & 1;
   if ((e = launch_run_end(r, st)) != hipSuccess) return hip_fail(e, "run_end launch");
   HIPCHK(hipStreamSynchronize(st));
   if (t_out) std::memcpy(t_out, h->h_t, n * sizeof(double));

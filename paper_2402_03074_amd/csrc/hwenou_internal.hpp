@@ -110,6 +110,27 @@ struct StepDt {
   bool done, failed;
 };
 template <int DIM>
+__device__ __forceinline__ void step_rule(const RunParams& R, const InstDev& I, const StepState& s,
+                                          int flag, StepDt& r) {  // r.ax, r.ay are given
+  r.s = s;
+  r.dt = 0.0;
+  r.failed = false;
+  r.done = s.done || flag || s.steps >= R.max_steps || s.t >= R.t_final * (1.0 - 1e-14);
+  if (r.done) return;
+  if (!isfinite(r.ax) || (DIM == 2 && !isfinite(r.ay))) {
+    r.done = r.failed = true;
+    return;
+  }
+  if (r.ax == 0.0 && (DIM == 1 || r.ay == 0.0))
+    r.dt = R.t_final - s.t;  // zero wave speed: every flux vanishes, the CFL bound is infinite
+  else if (DIM == 1)
+    r.dt = R.cfl * I.dx / r.ax;
+  else
+    r.dt = R.cfl / (r.ax / I.dx + r.ay / I.dy);
+  if (s.t + r.dt > R.t_final) r.dt = R.t_final - s.t;
+}
+
+template <int DIM>
 __device__ __forceinline__ StepDt step_dt(const StepControl& A, int inst, const InstDev& I) {
   StepDt r;
   const RunParams R = load_invariant(A.run);
@@ -138,22 +159,7 @@ __device__ __forceinline__ StepDt step_dt(const StepControl& A, int inst, const 
       if (DIM == 2) r.ay = fmax(r.ay, l[q].y);
     }
   }
-  r.s = s;
-  r.dt = 0.0;
-  r.failed = false;
-  r.done = s.done || flag || s.steps >= R.max_steps || s.t >= R.t_final * (1.0 - 1e-14);
-  if (r.done) return r;
-  if (!isfinite(r.ax) || (DIM == 2 && !isfinite(r.ay))) {
-    r.done = r.failed = true;
-    return r;
-  }
-  if (r.ax == 0.0 && (DIM == 1 || r.ay == 0.0))
-    r.dt = R.t_final - s.t;  // zero wave speed: every flux vanishes, the CFL bound is infinite
-  else if (DIM == 1)
-    r.dt = R.cfl * I.dx / r.ax;
-  else
-    r.dt = R.cfl / (r.ax / I.dx + r.ay / I.dy);
-  if (s.t + r.dt > R.t_final) r.dt = R.t_final - s.t;
+  step_rule<DIM>(R, I, s, flag, r);
   return r;
 }
 
@@ -227,6 +233,26 @@ hipError_t launch_stage_2d(int eq, int char_mode, bool mixed, bool scale_invaria
 // resident blocks per compute unit of a stage kernel at `threads` per block
 int occupancy_stage_1d(int eq, int char_mode, bool mixed, int threads);
 int occupancy_stage_2d(int eq, int char_mode, bool mixed, bool scale_invariant, int threads);
+
+// Runs of whole 1D steps in one launch, one block per instance.
+template <class TM>
+struct BlockRunArgs {
+  SchemeParams P;
+  const InstDev* inst;
+  const RunParams* run;
+  double* u;
+  TM* m;
+  StepState* st;     // [n_inst], read and written
+  int* flag;         // [n_inst], likewise
+  double* acc;       // [n_inst][kAlphaStride]: wave speed of the state, likewise
+  long long plane;
+  int n_inst, steps; // at most `steps` steps per launch
+};
+// cells of an instance that a block can hold: one tile per wave, and as many
+// waves as the kernels' registers let a CU hold (12 for Euler, 16 for scalar laws)
+constexpr int block_run_waves(int eq) { return eq == EQ_EULER ? 12 : 16; }
+hipError_t launch_block_run_1d(int eq, int char_mode, bool mixed, const void* args, int n_inst,
+                               int waves, hipStream_t s);
 
 // whole Runge-Kutta steps in 1D, one per launch; args: StepArgs<float or double>
 hipError_t launch_step_1d(int eq, int char_mode, bool mixed, const void* args, int waves,

@@ -110,6 +110,67 @@ __device__ __forceinline__ void ghost_lanes(int src, bool mirrored, double (&Uc)
   }
 }
 
+// One Runge-Kutta step of the tile that starts at cell `start`: load(cell, U, V)
+// reads a cell of the input.  On return lanes with `owner` hold their cell i
+// of the output in Uc, Vc; `ok` turns false where an owned stage output is not
+// physical.
+template <int EQ, bool CHAR, class TR, class TM, int NC, class Load>
+__device__ __forceinline__ void tile_step(const SchemeParams& P, const InstDev& I, int start,
+                                          int lane, double alpha_in, double idx, double dt,
+                                          Load load, int& i, bool& owner, bool& ok,
+                                          double (&Uc)[NC], TM (&Vc)[NC]) {
+  const int n = I.nx;
+  const bool periodic = I.bc[0] == BC_PERIODIC;
+  // Cell of this lane, and the cell it reads.  Lanes further out than any
+  // valid result reaches read some cell of the instance: past the last one
+  // periodic lanes stop at n + 5, the others at the two ghost cells that
+  // stencils of the instance's own cells use.
+  i = start - 5 + lane;
+  owner = lane >= 5 && lane < 5 + kStepWidth && i < n;
+  int ic, ie;
+  bool mir_c = false, mir_e = false;
+  if (periodic) {
+    const int last = n + 5;
+    auto wrap = [n](int j) {
+      j += j < 0 ? n : 0;
+      j += j < 0 ? n : 0;
+      j -= j >= n ? n : 0;
+      j -= j >= n ? n : 0;
+      return j;
+    };
+    ic = wrap(min(i, last));
+    ie = wrap(min(lane == 0 ? i - 1 : i + 1, last));
+  } else {
+    auto clamp = [n](int j) { return min(max(j, -2), n + 1); };
+    ic = source_cell(clamp(i), n, I.bc[0], I.bc[1], mir_c);
+    ie = source_cell(clamp(lane == 0 ? i - 1 : i + 1), n, I.bc[0], I.bc[1], mir_e);
+  }
+  const bool edge_lo = lane == 0, edge_hi = lane == 63;
+  double Uend[NC], Ub[NC];
+  TM Vend[NC], Mb[NC];
+  load(ic, Uc, Vc);
+  if (edge_lo || edge_hi) load(ie, Uend, Vend);
+  if constexpr (EQ == EQ_EULER) {
+    if (mir_c) mirror_cell<0, NC>(Uc, reinterpret_cast<TM(*)[NC]>(Vc), 1);
+    if (mir_e && (edge_lo || edge_hi))
+      mirror_cell<0, NC>(Uend, reinterpret_cast<TM(*)[NC]>(Vend), 1);
+  }
+  // lane that holds the cell a ghost lane images (boundary tiles only)
+  const bool ghosts = !periodic && (start < 5 || start + 58 >= n);
+  const int src = min(max(ic - start + 5, 0), 63);
+
+  rk_stage<EQ, CHAR, 0, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, edge_lo, edge_hi, Uc, Vc,
+                                    Ub, Mb);
+  if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
+  if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
+  rk_stage<EQ, CHAR, 1, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
+                                    Mb);
+  if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
+  if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
+  rk_stage<EQ, CHAR, 2, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
+                                    Mb);
+}
+
 template <int EQ, bool CHAR, class TR, class TM>
 __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1d_kernel(
     const StepArgs<TM> A) {
@@ -152,68 +213,22 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
       if (wk.start == 0 && lane == 0) write_step(A.ctl, inst, sd);
     }
     if (sd.done) continue;
-    const int n = I.nx;
-    const bool periodic = I.bc[0] == BC_PERIODIC;
-    // Cell of this lane, and the cell it reads.  Lanes further out than any
-    // valid result reaches read some cell of the instance: past the last one
-    // periodic lanes stop at n + 5, the others at the two ghost cells that
-    // stencils of the instance's own cells use.
-    int i = wk.start - 5 + lane;
-    const bool owner = lane >= 5 && lane < 5 + kStepWidth && i < n;
-    int ic, ie;
-    bool mir_c = false, mir_e = false;
-    if (periodic) {
-      const int last = n + 5;
-      auto wrap = [n](int j) {
-        j += j < 0 ? n : 0;
-        j += j < 0 ? n : 0;
-        j -= j >= n ? n : 0;
-        j -= j >= n ? n : 0;
-        return j;
-      };
-      ic = wrap(min(i, last));
-      ie = wrap(min(lane == 0 ? i - 1 : i + 1, last));
-    } else {
-      auto clamp = [n](int j) { return min(max(j, -2), n + 1); };
-      ic = source_cell(clamp(i), n, I.bc[0], I.bc[1], mir_c);
-      ie = source_cell(clamp(lane == 0 ? i - 1 : i + 1), n, I.bc[0], I.bc[1], mir_e);
-    }
     const double* u = A.u_in + I.offset;
     const TM* m = A.m_in + I.offset;
-    const bool edge_lo = lane == 0, edge_hi = lane == 63;
-    double Uc[NC], Uend[NC], Ub[NC];
-    TM Vc[NC], Vend[NC], Mb[NC];
+    int i;
+    bool owner;
+    double Uc[NC];
+    TM Vc[NC];
+    tile_step<EQ, CHAR, TR, TM, NC>(
+        P, I, wk.start, lane, alpha_in, idx, dt,
+        [&](int c, double (&U)[NC], TM (&V)[NC]) {
 #pragma unroll
-    for (int k = 0; k < NC; ++k) {
-      Uc[k] = u[k * plane + ic];
-      Vc[k] = m[k * plane + ic];
-    }
-    if (edge_lo || edge_hi) {
-#pragma unroll
-      for (int k = 0; k < NC; ++k) {
-        Uend[k] = u[k * plane + ie];
-        Vend[k] = m[k * plane + ie];
-      }
-    }
-    if constexpr (EQ == EQ_EULER) {
-      if (mir_c) mirror_cell<0, NC>(Uc, reinterpret_cast<TM(*)[NC]>(Vc), 1);
-      if (mir_e && (edge_lo || edge_hi))
-        mirror_cell<0, NC>(Uend, reinterpret_cast<TM(*)[NC]>(Vend), 1);
-    }
-    // lane that holds the cell a ghost lane images (boundary tiles only)
-    const bool ghosts = !periodic && (wk.start < 5 || wk.start + 58 >= n);
-    const int src = min(max(ic - wk.start + 5, 0), 63);
-
-    rk_stage<EQ, CHAR, 0, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, edge_lo, edge_hi, Uc, Vc,
-                                      Ub, Mb);
-    if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
-    if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
-    rk_stage<EQ, CHAR, 1, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
-                                      Mb);
-    if (owner) ok = physical_state<EQ, NC>(Uc) && ok;
-    if (ghosts) ghost_lanes<EQ, TM, NC>(src, mir_c, Uc, Vc);
-    rk_stage<EQ, CHAR, 2, TR, TM, NC>(P, alpha_in, idx, dt, Uend, Vend, false, false, Uc, Vc, Ub,
-                                      Mb);
+          for (int k = 0; k < NC; ++k) {
+            U[k] = u[k * plane + c];
+            V[k] = m[k * plane + c];
+          }
+        },
+        i, owner, ok, Uc, Vc);
     if (owner) {
       const long long o = I.offset + i;
 #pragma unroll
@@ -227,6 +242,141 @@ __global__ __launch_bounds__(256, (min_waves_step1d<EQ, CHAR, TR>())) void step1
     }
   }
   flush();
+}
+
+// A run of steps of an instance that one block can hold (one tile per wave):
+// the state stays in LDS from step to step, a step is its three stages, the
+// exchange through LDS and one barrier, and the block takes the wave speed and
+// forms the time step itself.  Such an instance is bound by the latency of the
+// chain of launches otherwise: 200 cells of advection take 4.5 us per step with
+// one launch per step and 1.5 us here.
+template <int EQ, bool CHAR, class TR, class TM>
+__global__ __launch_bounds__(64 * block_run_waves(EQ)) void block_run_kernel(
+    const BlockRunArgs<TM> A) {
+  constexpr int NC = EQ == EQ_EULER ? 3 : 1;
+  constexpr int WAVES = block_run_waves(EQ), CELLS = WAVES * kStepWidth;
+  __shared__ double Us[2][NC][CELLS];
+  __shared__ TM Vs[2][NC][CELLS];
+  __shared__ double speed[2][WAVES];
+  __shared__ int bad[2][WAVES];
+  const int inst = blockIdx.x, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int waves = blockDim.x >> 6;
+  const InstDev I = load_invariant(A.inst + inst);
+  const RunParams R = load_invariant(A.run);
+  StepState s = A.st[inst];
+  int flag = A.flag[inst];
+  StepDt d;
+  d.ax = A.acc[kAlphaStride * inst];
+  d.ay = 0.0;
+  const int n = I.nx, start = wave * kStepWidth;
+  const bool active = start < n;
+  const double idx = uniform(1.0 / I.dx);
+  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      Us[0][k][c] = A.u[k * A.plane + I.offset + c];
+      Vs[0][k][c] = A.m[k * A.plane + I.offset + c];
+    }
+  }
+  __syncthreads();
+  int cur = 0;
+  bool failed = false;
+  for (int step = 0; step < A.steps; ++step) {
+    step_rule<1>(R, I, s, flag, d);  // the same on every thread
+    if (d.done) {
+      failed = d.failed;
+      break;
+    }
+    double mx = 0.0;
+    bool ok = true;
+    if (active) {
+      int i;
+      bool owner;
+      double Uc[NC];
+      TM Vc[NC];
+      tile_step<EQ, CHAR, TR, TM, NC>(
+          A.P, I, start, lane, uniform(d.ax), idx, uniform(d.dt),
+          [&](int c, double (&U)[NC], TM (&V)[NC]) {
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+              U[k] = Us[cur][k][c];
+              V[k] = Vs[cur][k][c];
+            }
+          },
+          i, owner, ok, Uc, Vc);
+      if (owner) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          Us[cur ^ 1][k][i] = Uc[k];
+          Vs[cur ^ 1][k][i] = Vc[k];
+        }
+        double sx, sy;
+        ok = wave_speeds<EQ, NC>(A.P, Uc, sx, sy) && ok;
+        mx = sx;
+      }
+    }
+    // two sets of slots: a wave may write the next step's before the last wave
+    // has read this one's
+    const unsigned long long all_ok = __ballot(ok);
+    mx = wave_max_dpp(fmax(0.0, mx));
+    if (lane == 63) {
+      speed[cur][wave] = mx;
+      bad[cur][wave] = ~all_ok != 0;
+    }
+    __syncthreads();
+    d.ax = 0.0;
+    for (int w = 0; w < waves; ++w) {
+      d.ax = fmax(d.ax, speed[cur][w]);
+      flag |= bad[cur][w];
+    }
+    s.t += d.dt;
+    s.steps += 1;
+    cur ^= 1;
+  }
+  for (int c = threadIdx.x; c < n; c += blockDim.x) {
+#pragma unroll
+    for (int k = 0; k < NC; ++k) {
+      A.u[k * A.plane + I.offset + c] = Us[cur][k][c];
+      A.m[k * A.plane + I.offset + c] = Vs[cur][k][c];
+    }
+  }
+  if (threadIdx.x == 0) {
+    s.done = s.done || failed;
+    A.st[inst] = s;
+    A.flag[inst] = flag | (failed ? 1 : 0);
+    A.acc[kAlphaStride * inst] = d.ax;
+  }
+}
+
+template <int EQ, bool CHAR, class TR, class TM>
+static hipError_t launch_block(const void* args, int n_inst, int waves, hipStream_t s) {
+  const auto& a = *static_cast<const BlockRunArgs<TM>*>(args);
+  hipLaunchKernelGGL((block_run_kernel<EQ, CHAR, TR, TM>), dim3(n_inst), dim3(64 * waves), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_run_1d(int eq, int char_mode, bool mixed, const void* args, int n_inst,
+                               int waves, hipStream_t s) {
+  if (waves > block_run_waves(eq)) return hipErrorInvalidValue;
+  if (mixed) {
+    switch (eq) {
+      case EQ_ADVECTION:
+        return launch_block<EQ_ADVECTION, false, float, float>(args, n_inst, waves, s);
+      case EQ_BURGERS: return launch_block<EQ_BURGERS, false, float, float>(args, n_inst, waves, s);
+      default:
+        return char_mode ? launch_block<EQ_EULER, true, float, float>(args, n_inst, waves, s)
+                         : launch_block<EQ_EULER, false, float, float>(args, n_inst, waves, s);
+    }
+  }
+  switch (eq) {
+    case EQ_ADVECTION:
+      return launch_block<EQ_ADVECTION, false, double, double>(args, n_inst, waves, s);
+    case EQ_BURGERS: return launch_block<EQ_BURGERS, false, double, double>(args, n_inst, waves, s);
+    default:
+      return char_mode ? launch_block<EQ_EULER, true, double, double>(args, n_inst, waves, s)
+                       : launch_block<EQ_EULER, false, double, double>(args, n_inst, waves, s);
+  }
 }
 
 template <int EQ, bool CHAR, class TR, class TM>

@@ -58,9 +58,28 @@ def test_whole_steps_equal_stages(sides, eq, char, precision):
     if eq != "euler" and "reflective" in sides:
         pytest.skip("walls are defined for the Euler equations")
     print(f"[gpu] whole steps {sides} {eq} {char} {precision}", flush=True)
-    for steps in (1, 2, 3):  # odd counts bring the state back from the scratch buffers
+    # odd counts bring the state back from the scratch buffers
+    _check(SIZES, (1, 2, 3), sides, eq, char, precision)
+
+
+# grids that one block holds through a run of steps: up to 12 tiles of 54 cells
+# for Euler, 16 for the scalar laws; one more cell takes one launch per step
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("eq,char,most", [("advection", 0, 864), ("burgers", 0, 864),
+                                          ("euler", 0, 648), ("euler", 1, 648)])
+@pytest.mark.parametrize("sides", SIDES[:4], ids="-".join)
+def test_block_runs_equal_stages(sides, eq, char, most, precision):
+    if eq != "euler" and "reflective" in sides:
+        pytest.skip("walls are defined for the Euler equations")
+    print(f"[gpu] block runs {sides} {eq} {char} {precision}", flush=True)
+    for sizes in ([3], [54], [55], [most], [most + 1], [4, 59, 108, most - 1, 200]):
+        _check(sizes, (1, 5), sides, eq, char, precision)
+
+
+def _check(sizes, counts, sides, eq, char, precision):
+    for steps in counts:
         off, insts, us, ms = 0, [], [], []
-        for k, n in enumerate(SIZES):
+        for k, n in enumerate(sizes):
             insts.append(H.make_inst(n, 1, (0.0, 1.0), sides, offset=off))
             u, m = _data(eq, n, 100 * k + steps)
             us.append(u)
@@ -72,16 +91,18 @@ def test_whole_steps_equal_stages(sides, eq, char, precision):
         ub, mb = to_gpu(u0), to_gpu(m0, S.mom_dtype)
         t, n_steps = S.advance(ua, ma, 0.3, 1e30, steps)
         te = _eager(S, insts, ub, mb, 0.3, steps)
-        assert n_steps == [steps] * len(SIZES) and np.array_equal(np.array(t), te)
+        assert n_steps == [steps] * len(sizes) and np.array_equal(np.array(t), te)
         assert torch.equal(ua, ub) and torch.equal(ma, mb)
         S.close()
 
 
-def test_instances_stop_after_odd_and_even_steps():
+@pytest.mark.parametrize("sizes", [[40, 61, 90, 333, 700], [40, 61, 90, 333, 600]],
+                         ids=["steps", "block runs"])
+def test_instances_stop_after_odd_and_even_steps(sizes):
     """Instances that reach t_final after different step counts: each ends in
     the caller's arrays, as it does alone."""
     insts, us, ms, off = [], [], [], 0
-    for k, n in enumerate([40, 61, 90, 333, 700]):
+    for k, n in enumerate(sizes):
         u, m = _data("euler", n, 7 + k)
         insts.append(H.make_inst(n, 1, (0.0, 1.0), "periodic", offset=off))
         us.append(u)
