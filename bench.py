@@ -47,7 +47,8 @@ COMMON_SOURCES = ["paper_2402_03074_amd/csrc/hwenou_device.hpp",
                   "paper_2402_03074_amd/csrc/hwenou_internal.hpp",
                   "paper_2402_03074_amd/csrc/hwenou_api.hip",
                   "paper_2402_03074_amd/build.py"]
-KERNEL_SOURCES = ["paper_2402_03074_amd/csrc/stage2d.hip"] + COMMON_SOURCES
+KERNEL_SOURCES = ["paper_2402_03074_amd/csrc/stage2d.hip",
+                  "paper_2402_03074_amd/csrc/field2d.hpp"] + COMMON_SOURCES
 # rocprofv3 counter summaries (profiles/) per stage kernel and the workload
 # they were taken on
 COUNTERS = {

@@ -12,7 +12,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libhwenou.so")
-SOURCES = ["hwenou_api.hip", "stage1d.hip", "step1d.hip", "stage2d.hip", "aux.hip", "noalloc.hip"]
+SOURCES = ["hwenou_api.hip", "stage1d.hip", "step1d.hip", "stage2d.hip", "pair2d.hip",
+           "aux.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("HWENOU_ARCH", "gfx950")
 
@@ -28,7 +29,8 @@ FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
 # better than the default on a batch of 512 grids.
 SOURCE_FLAGS = {"stage2d.hip": ["-mllvm", "-amdgpu-sched-strategy=iterative-ilp"],
                 "stage1d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-                "step1d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+                "step1d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+                "pair2d.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 
 def _compile(src, verbose, extra):

@@ -235,6 +235,32 @@ struct Field {
   double c[15], x[5];
 };
 
+// The FP64 stage's results are the same bits from every kernel that computes a
+// cell (one wave or a pair of waves per run).  What the compiler fuses into one
+// rounding depends on the code around, so the steps of the FP64 reconstruction
+// end in values it cannot see through (pin: no instruction), and the mapping's
+// sums of products say which product is fused (mad).  The mixed kernels, of
+// which there is one per cell, spill with mad as fma.
+template <class T, int N>
+__device__ __forceinline__ void pin(T (&x)[N]) {
+  if constexpr (sizeof(T) == 8) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) asm("" : "+v"(x[n]));
+  }
+}
+template <class T, int M, int N>
+__device__ __forceinline__ void pin(T (&x)[M][N]) {
+#pragma unroll
+  for (int m = 0; m < M; ++m) pin(x[m]);
+}
+template <class T>
+__device__ __forceinline__ T mad(T a, T b, T c) {
+  if constexpr (sizeof(T) == 8)
+    return fma(a, b, c);
+  else
+    return a * b + c;
+}
+
 template <class TR>
 __device__ __forceinline__ void make_field(const Sten2& S, Field& F) {
   p0_coeffs_2d<TR>(S, F.c);
@@ -243,6 +269,10 @@ __device__ __forceinline__ void make_field(const Sten2& S, Field& F) {
   F.x[2] = S.u[4];
   F.x[3] = S.u[5];
   F.x[4] = S.u[7];
+  if constexpr (sizeof(TR) == 8) {
+    pin(F.c);
+    pin(F.x);
+  }
 }
 
 // F = A + s B
@@ -251,6 +281,8 @@ __device__ __forceinline__ void add_fields(const Field& A, double s, const Field
   for (int n = 0; n < 15; ++n) F.c[n] = fma(s, B.c[n], A.c[n]);
 #pragma unroll
   for (int n = 0; n < 5; ++n) F.x[n] = fma(s, B.x[n], A.x[n]);
+  pin(F.c);
+  pin(F.x);
 }
 
 // Scalar HWENO reconstruction of one field -> combined coefficients
@@ -261,6 +293,10 @@ __device__ __forceinline__ void recon_field(const SchemeParams& P, const Field& 
   const double asum = fabs(F.x[0]) + fabs(F.x[1]) + fabs(u5) + fabs(F.x[3]) + fabs(F.x[4]);
   hweno_2d<TR, SI, FOLD>(P, F.c, u5, u5 - F.x[1], F.x[3] - u5, u5 - F.x[0], F.x[4] - u5, asum, C,
                          a_out);
+  if constexpr (sizeof(TR) == 8) {
+    pin(C);
+    if constexpr (FOLD) asm("" : "+v"(*a_out));
+  }
 }
 
 // S += s * (stencil of component k); first = true: S = s * (...)
@@ -440,8 +476,8 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
       for (int n = 0; n < 15; ++n) {
         const TR p0 = S[n];
         const TR f = n < 3 ? (TR)1 : a3;
-        S[n] = f * C[n] + p0;
-        D[n] = f * C[n] - p0;
+        S[n] = mad(f, C[n], p0);
+        D[n] = mad(f, C[n], -p0);
       }
     }
   }
@@ -483,9 +519,9 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
 #pragma unroll
     for (int n = 0; n < 15; ++n) {
       const TR f1 = n < 3 ? (TR)1 : ta1, fh = n < 3 ? th : tha1;
-      Cc[0][n] = f1 * C1[n] + S[n];
-      Cc[nd][n] = tun * Cc[0][n] + tc * D[n];
-      Cc[3][n] = fh * C1[n] + (tunc * D[n] + tH * S[n]);
+      Cc[0][n] = mad(f1, C1[n], S[n]);
+      Cc[nd][n] = mad(tun, Cc[0][n], tc * D[n]);
+      Cc[3][n] = mad(fh, C1[n], mad(tunc, D[n], tH * S[n]));
     }
   }
   if constexpr (!OVERLAP12) __builtin_amdgcn_sched_barrier(0);
@@ -501,8 +537,8 @@ __device__ __forceinline__ void char_sweep(const SchemeParams& P, const Prim& pr
 #pragma unroll
     for (int n = 0; n < 15; ++n) {
       const TR f2 = n < 3 ? (TR)1 : a2, fu = n < 3 ? tut : uta2;
-      Cc[td][n] = f2 * C[n] + tut * Cc[0][n];
-      Cc[3][n] += fu * C[n];
+      Cc[td][n] = mad(f2, C[n], tut * Cc[0][n]);
+      Cc[3][n] = mad(fu, C[n], Cc[3][n]);
     }
   }
 }

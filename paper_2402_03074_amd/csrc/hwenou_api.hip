@@ -87,7 +87,8 @@ struct hwenou_handle {
   int slots = 1;  // wave-speed accumulators per instance
   WorkItem* d_work = nullptr;        // with d_work_ptr behind it
   int* d_work_ptr = nullptr;
-  int n_waves = 0;
+  int n_waves = 0;      // runs; of pairs of waves if `pairs`
+  bool pairs = false;   // 2D: a pair of waves per run
   bool work_dirty = true;
 };
 
@@ -174,8 +175,23 @@ int build_work(hwenou_handle* h) {
   drop_graph(h);  // the captured step graph holds the old work lists
   std::vector<WorkItem> items;
   std::vector<int> ptr;
+  // a pair of waves per run, unless the caller has set the launch shape
+  h->pairs = false;
+  if (h->dim == 2 && h->waves_per_cu <= 0 && h->rows_per_item <= 0) {
+    long long total = 0;
+    int strips = 0, ny = 0;
+    for (const hwenou_inst& I : h->inst) {
+      const int ns = (I.nx + kStripWidth - 1) / kStripWidth;
+      total += (long long)ns * I.ny;
+      if ((long long)ns * I.ny > (long long)strips * ny) {
+        strips = ns;
+        ny = I.ny;
+      }
+    }
+    h->pairs = use_pairs_2d(h->desc.eq, h->desc.char_decomp, h->mixed, total, strips, ny, h->n_cu);
+  }
   // default: as many waves per compute unit as can be resident at once
-  int wpc = h->waves_per_cu;
+  int wpc = h->pairs ? 2 : h->waves_per_cu;
   if (wpc <= 0) {
     const int chr = h->desc.eq == HWENOU_EQ_EULER ? h->desc.char_decomp : 0;
     const bool si = h->desc.weights == HWENOU_W_SCALE_INVARIANT;
@@ -387,7 +403,8 @@ int launch_stage(hwenou_handle* h, int s, const double* dt, const double* alpha,
     if (h->dim == 1)
       e = launch_stage_1d(h->desc.eq, chr, false, &A, (h->n_waves + 3) / 4, 256, st);
     else
-      e = launch_stage_2d(h->desc.eq, chr, false, si, &A, h->n_waves, 64, st);
+      e = h->pairs ? launch_pair_2d(si, A, h->n_waves, st)
+                   : launch_stage_2d(h->desc.eq, chr, false, si, &A, h->n_waves, 64, st);
   }
   if (e != hipSuccess) return hip_fail(e, "stage kernel launch");
   return HWENOU_OK;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "hwenou_device.hpp"
 
 namespace hwenou {
@@ -229,6 +231,31 @@ hipError_t launch_stage_1d(int eq, int char_mode, bool mixed, const void* args, 
 // scale_invariant: the default weights, compiled into their own 2D kernels
 hipError_t launch_stage_2d(int eq, int char_mode, bool mixed, bool scale_invariant,
                            const void* args, int blocks, int threads, hipStream_t s);
+
+// the same stage, direction-split characteristic Euler in FP64, by pairs of waves
+// (pair2d.hip)
+hipError_t launch_pair_2d(bool scale_invariant, const StageArgs<double>& args, int blocks,
+                          hipStream_t s);
+
+// Whether a 2D handle's stages run by pairs of waves, and the resident blocks
+// its work lists are cut for: `total` strip-rows over all grids, of which the
+// largest has `strips` strips of `ny` rows.  A pair takes about 0.55 of a
+// single wave's time per row, on two SIMDs, so half as many runs of twice the
+// rows are in flight: pairs win where runs are so short that their two boundary
+// rows and their start weigh most.  Measured, one wave / a pair per run, us per
+// Runge-Kutta step (FP64): 60 x 60 (1 row per run / 1 row) 70 / 56,
+// 131 x 97 (1 / 1) 73 / 62, 256 x 256 (2 / 3) 110 / 99, 400 x 300 (3 / 5)
+// 142 / 135, 512 x 512 (5 / 10) 201 / 221.
+constexpr int kPairMaxRows = 5;
+inline bool use_pairs_2d(int eq, int char_mode, bool mixed, long long total, int strips, int ny,
+                         int n_cu) {
+  if (eq != EQ_EULER || char_mode != 1 || mixed) return false;
+  const long long pairs = 2LL * n_cu;
+  const long long rows = total > (long long)strips * ny
+                             ? (total + pairs - 1) / pairs  // several grids: equal runs
+                             : (ny + std::max(1LL, pairs / strips) - 1) / std::max(1LL, pairs / strips);
+  return rows <= kPairMaxRows;
+}
 
 // resident blocks per compute unit of a stage kernel at `threads` per block
 int occupancy_stage_1d(int eq, int char_mode, bool mixed, int threads);

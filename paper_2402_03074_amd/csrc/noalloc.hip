@@ -134,13 +134,17 @@ extern "C" int hwenou_step_noalloc(const hwenou_desc* d, const hwenou_inst* inst
   int wpc = dim == 1 ? 4 * occupancy_stage_1d(d->eq, chr, mixed, 256)
                      : occupancy_stage_2d(d->eq, chr, mixed, si, 64);
   if (wpc <= 0) wpc = 4;
+  const int strips = (nx + kStripWidth - 1) / kStripWidth;
+  const bool pairs =
+      dim == 2 && use_pairs_2d(d->eq, chr, mixed, (long long)strips * ny, strips, ny, di->n_cu);
+  if (pairs) wpc = 2;
   const long long target = (long long)di->n_cu * wpc;
   int n_items, n_waves, chunks = 0;
   if (dim == 1) {
     n_items = (int)((cells + kStripWidth - 1) / kStripWidth);
     n_waves = (int)std::min<long long>(n_items, target);
   } else {
-    const int ns = (nx + kStripWidth - 1) / kStripWidth;
+    const int ns = strips;
     // the fewest rows per run that keep the runs within the resident waves, down
     // to one, as in the handle's lists for one grid
     const int fit = (int)std::min<long long>(std::max<long long>(1, target / ns), ny);
@@ -193,9 +197,14 @@ extern "C" int hwenou_step_noalloc(const hwenou_desc* d, const hwenou_inst* inst
       A.m_in = min_[s];
       A.u_out = uout[s];
       A.m_out = mout[s];
-      const hipError_t le =
-          dim == 1 ? launch_stage_1d(d->eq, chr, mixed, &A, (n_waves + 3) / 4, 256, st)
-                   : launch_stage_2d(d->eq, chr, mixed, si, &A, n_waves, 64, st);
+      hipError_t le;
+      if (dim == 1)
+        le = launch_stage_1d(d->eq, chr, mixed, &A, (n_waves + 3) / 4, 256, st);
+      else if constexpr (sizeof(TM) == 8)
+        le = pairs ? launch_pair_2d(si, A, n_waves, st)
+                   : launch_stage_2d(d->eq, chr, false, si, &A, n_waves, 64, st);
+      else
+        le = launch_stage_2d(d->eq, chr, true, si, &A, n_waves, 64, st);
       if (le != hipSuccess) return le;
     }
     return hipSuccess;

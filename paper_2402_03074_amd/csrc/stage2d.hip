@@ -252,6 +252,7 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
           recon_field<TR, SI>(P, F, Cc[k]);
         }
       }
+      if constexpr (SPLIT && !IFACE) pin(Cc);
       // y-edges at (xi_G, -+1/2), interior values for g (and f when the
       // reconstruction is shared), y-fluxes at y_{j-1/2}
       TR F1n_s[NC], F2n[NC], F3n[NC];  // new row: bottom-flux terms
@@ -408,6 +409,7 @@ __global__ __launch_bounds__(64, 1) void stage2d_kernel(const StageArgs<TM> A) {
         if constexpr (SPLIT)
           char_sweep<0, SI, false, !IFACE, TR, TM, !IFACE && SI && sizeof(TR) == 8>(P, pr, B, sb, sc, st, lane,
                                                                       Cc, c1buf, pbuf, true);
+        if constexpr (SPLIT && !IFACE) pin(Cc);
         double F1x[NC];
         TR F2x[NC], F3x[NC];
 #pragma unroll
