@@ -70,7 +70,7 @@ WORKLOADS = {
     "euler1d-65536": "1D Euler N = 65536 transmissive on [0,1], seeded 16-interface "
                      "shock tube with a density wave, CFL 0.6, characteristic-wise",
     "euler1d-batch512": "512 independent 1D Euler shock tubes, N log-uniform in "
-                        "[256, 65536], one persistent launch per stage, per-instance dt",
+                        "[256, 65536], one persistent launch per step, per-instance dt",
     "euler2d-batch64": "64 independent 2D Euler vortex+quadrant grids, sides log-uniform "
                        "in [256, 1024], one persistent launch per stage, per-instance dt",
 }
