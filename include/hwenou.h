@@ -165,7 +165,7 @@ int hwenou_stage(hwenou_handle* h, int s, const double* dt_dev, const double* al
  * CFL number (0.6 in Section 3) but not the formula; this is the usual one.
  * alpha and dt stay on the device.  In 1D a whole step is one launch on the
  * handle's stream, or a run of steps where one block holds an instance (up to
- * 648 cells for Euler and 864 for scalar laws, and no more instances than
+ * 432 cells for Euler and 864 for scalar laws, and no more instances than
  * compute units), unless an instance has exactly one periodic side; in 2D,
  * and for such 1D handles, a step is one launch per stage, and runs of eight
  * steps are replayed from a HIP graph, which is captured on the first call of

@@ -275,9 +275,14 @@ struct BlockRunArgs {
   long long plane;
   int n_inst, steps; // at most `steps` steps per launch
 };
-// cells of an instance that a block can hold: one tile per wave, and as many
-// waves as the kernels' registers let a CU hold (12 for Euler, 16 for scalar laws)
-constexpr int block_run_waves(int eq) { return eq == EQ_EULER ? 12 : 16; }
+// Waves of a block that holds an instance, one tile per wave.  All tiles share
+// one CU's four SIMDs there, where a launch per step gives each tile its own, so
+// the line lies where a SIMD gets its third tile for Euler and not before the
+// block is full for the scalar laws.  Measured, launch per step / run of steps,
+// us per 12 steps: Euler characteristic 4 tiles 113 / 78, 8 tiles 119 / 114,
+// 12 tiles 120 / 158; component-wise (4 steps) 47 / 38, 50 / 48, 50 / 60;
+// Burgers (20 steps) 8 tiles 120 / 67, 16 tiles 124 / 105.
+constexpr int block_run_waves(int eq) { return eq == EQ_EULER ? 8 : 16; }
 hipError_t launch_block_run_1d(int eq, int char_mode, bool mixed, const void* args, int n_inst,
                                int waves, hipStream_t s);
 

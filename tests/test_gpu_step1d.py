@@ -62,17 +62,17 @@ def test_whole_steps_equal_stages(sides, eq, char, precision):
     _check(SIZES, (1, 2, 3), sides, eq, char, precision)
 
 
-# grids that one block holds through a run of steps: up to 12 tiles of 54 cells
+# grids that one block holds through a run of steps: up to 8 tiles of 54 cells
 # for Euler, 16 for the scalar laws; one more cell takes one launch per step
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("eq,char,most", [("advection", 0, 864), ("burgers", 0, 864),
-                                          ("euler", 0, 648), ("euler", 1, 648)])
+                                          ("euler", 0, 432), ("euler", 1, 432)])
 @pytest.mark.parametrize("sides", SIDES[:4], ids="-".join)
 def test_block_runs_equal_stages(sides, eq, char, most, precision):
     if eq != "euler" and "reflective" in sides:
         pytest.skip("walls are defined for the Euler equations")
     print(f"[gpu] block runs {sides} {eq} {char} {precision}", flush=True)
-    for sizes in ([3], [54], [55], [most], [most + 1], [4, 59, 108, most - 1, 200]):
+    for sizes in ([3], [54], [55], [most], [most + 1], [4, 59, 108, most - 1, 200], [648]):
         _check(sizes, (1, 5), sides, eq, char, precision)
 
 
