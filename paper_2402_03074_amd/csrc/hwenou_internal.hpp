@@ -237,24 +237,29 @@ hipError_t launch_stage_2d(int eq, int char_mode, bool mixed, bool scale_invaria
 hipError_t launch_pair_2d(bool scale_invariant, const StageArgs<double>& args, int blocks,
                           hipStream_t s);
 
-// Whether a 2D handle's stages run by pairs of waves, and the resident blocks
-// its work lists are cut for: `total` strip-rows over all grids, of which the
-// largest has `strips` strips of `ny` rows.  A pair takes about 0.55 of a
-// single wave's time per row, on two SIMDs, so half as many runs of twice the
-// rows are in flight: pairs win where runs are so short that their two boundary
-// rows and their start weigh most.  Measured, one wave / a pair per run, us per
-// Runge-Kutta step (FP64): 60 x 60 (1 row per run / 1 row) 70 / 56,
-// 131 x 97 (1 / 1) 73 / 62, 256 x 256 (2 / 3) 110 / 99, 400 x 300 (3 / 5)
-// 142 / 135, 512 x 512 (5 / 10) 201 / 221.
+// Whether a 2D handle's stages run by pairs of waves (two resident per compute
+// unit, against four single waves): `total` strip-rows over all grids, of which
+// the largest has `strips` strips of `ny` rows.  With r rows per run a stage
+// takes about 34 + 35 r us per Runge-Kutta step by single waves and 40 + 19 r by
+// pairs, whose runs are up to twice as long, since half as many are in flight.
+// So pairs win where rounding to whole rows leaves them less than twice the rows
+// of a single wave, and runs are short.  Measured, single waves / pairs (rows per
+// run), us per step: 60 x 60 70 / 56 (1 / 1), 131 x 97 76 / 61 (1 / 1),
+// 900 x 100 113 / 103 (2 / 3), 256 x 256 110 / 99 (2 / 3), 500 x 200 115 / 119
+// (2 / 4), 400 x 300 142 / 135 (3 / 5), 512 x 512 201 / 221 (5 / 10), 6 grids of
+// 40^2 to 150^2 85 / 108 (1 / 2), 24 grids of 60^2 109 / 97 (2 / 3).
 constexpr int kPairMaxRows = 5;
 inline bool use_pairs_2d(int eq, int char_mode, bool mixed, long long total, int strips, int ny,
                          int n_cu) {
   if (eq != EQ_EULER || char_mode != 1 || mixed) return false;
-  const long long pairs = 2LL * n_cu;
-  const long long rows = total > (long long)strips * ny
-                             ? (total + pairs - 1) / pairs  // several grids: equal runs
-                             : (ny + std::max(1LL, pairs / strips) - 1) / std::max(1LL, pairs / strips);
-  return rows <= kPairMaxRows;
+  const bool several = total > (long long)strips * ny;
+  const auto rows = [&](long long runs) {
+    if (several) return (total + runs - 1) / runs;  // several grids: equal runs
+    const long long per_strip = std::max(1LL, runs / strips);
+    return (ny + per_strip - 1) / per_strip;
+  };
+  const long long pair = rows(2LL * n_cu);
+  return pair <= kPairMaxRows && pair < 2 * rows(4LL * n_cu);
 }
 
 // resident blocks per compute unit of a stage kernel at `threads` per block

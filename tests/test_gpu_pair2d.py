@@ -1,7 +1,7 @@
 """2D Euler stages in FP64 by pairs of waves against one wave per run.
 
-Grids whose runs are at most five rows take a pair of waves per run (one for
-each direction's sweep); a launch shape set by hand takes one wave.  Both
+Grids whose runs are short take a pair of waves per run (one for each
+direction's sweep); a launch shape set by hand takes one wave.  Both
 evaluate the same expressions on the same values, so they agree bitwise: at the
 edges of the strips, with one row and with several per run, at every boundary,
 with several grids in one launch and over whole steps."""
@@ -13,10 +13,10 @@ import paper_2402_03074_amd as H
 
 pytestmark = pytest.mark.gpu
 
-# a strip is 62 columns; 3 rows or columns are the fewest; the last two grids
-# have several rows per run, the last also an uneven last run
+# a strip is 62 columns; 3 rows or columns are the fewest; (400, 203) and the 24 grids
+# have several rows per run, those of the 24 going on in the next grid
 GRIDS = [[(3, 3)], [(62, 5)], [(63, 4)], [(125, 3)], [(131, 97)], [(400, 203)],
-         [(40, 40), (63, 21), (5, 130)]]
+         [(40, 40), (63, 21), (5, 130)], [(60, 61)] * 24]
 SIDES = ["periodic", ("transmissive", "reflective", "reflective", "transmissive")]
 
 
@@ -34,7 +34,7 @@ def _state(grids, seed):
 
 @pytest.mark.parametrize("weights", ["scale_invariant", "zq"])
 @pytest.mark.parametrize("sides", SIDES, ids=["periodic", "walls"])
-@pytest.mark.parametrize("grids", GRIDS, ids=str)
+@pytest.mark.parametrize("grids", GRIDS, ids=lambda g: f"{len(g)}x{g[0]}")
 def test_pairs_equal_single_waves(grids, sides, weights):
     print(f"[gpu] pairs {grids} {sides} {weights}", flush=True)
     u0, m0 = _state(grids, 11)
